@@ -63,12 +63,13 @@ struct BatchArgs {
 };
 
 // Kernels for items whose dimension lies in [dlo, dhi] and whose target's
-// regeneration distribution is of kind mu.
+// regeneration distribution is of kind mu; split: the slab from the scalar
+// cache and LDS (MixRows).
 struct BatchKernels {
     const void *persistent = nullptr;
     const void *per_target = nullptr;
 };
-BatchKernels find_batch_kernels(int dlo, int dhi, int mu);
+BatchKernels find_batch_kernels(int dlo, int dhi, int mu, bool split);
 
 hipError_t launch_batch_zero(const BatchArgs &b, hipStream_t s);
 hipError_t launch_batch_reduce(const BatchArgs &b, hipStream_t s);

@@ -121,6 +121,7 @@ struct Bucket {
     int dlo, dhi, mu;
     BatchKernels k;
     size_t item_begin, item_count;
+    size_t lds;   // dynamic LDS: the largest LDS part of its targets' slabs
     int grid;
 };
 
@@ -179,18 +180,22 @@ restore_status build_items(restore_batch *b, hipStream_t s) {
     else ranges = {{1, 16}};
     std::vector<WorkItem> all;
     b->buckets.clear();
+    // the slab half from LDS once the batch has waves to issue side by side,
+    // as for single targets (restore_api.cpp)
+    const bool split = b->lay.total_chains >= (1LL << 16);
     for (int mu : {(int)MU_UNIFORM, (int)MU_GMM})
     for (auto r : ranges) {
         Bucket bk{};
         bk.dlo = r.first;
         bk.dhi = r.second;
         bk.mu = mu;
-        bk.k = find_batch_kernels(r.first, r.second, mu);
+        bk.k = find_batch_kernels(r.first, r.second, mu, split);
         if (!bk.k.persistent) return fail(RESTORE_E_UNSUPPORTED, "batch kernels for this dimension range are not built");
         std::vector<std::pair<double, WorkItem>> items;
         for (int i = 0; i < b->n; ++i) {
             const BatchTarget &t = b->targets[i];
             if (t.d < r.first || t.d > r.second || t.mu_kind != mu) continue;
+            if (split) bk.lds = std::max(bk.lds, sizeof(float) * (size_t)t.K * mix_stride(t.d));
             // cost of a tile ~ chains x (components x (d^2 + 3d) + mu components x 3d) per step
             const double per_chain = (double)t.K * (t.d * t.d + 3 * t.d + 7) +
                                      (mu == MU_GMM ? (double)t.mu_comp * (3 * t.d + 9) : 0.0);
@@ -211,7 +216,7 @@ restore_status build_items(restore_batch *b, hipStream_t s) {
         bk.item_count = items.size();
         for (auto &it : items) all.push_back(it.second);
         int per_cu = 0;
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, bk.k.persistent, block, 0);
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, bk.k.persistent, block, bk.lds);
         if (e != hipSuccess) return hip_fail(e, "occupancy query");
         bk.grid = std::max(1, per_cu) * b->n_cu;
         if (bk.item_count) b->buckets.push_back(bk);
@@ -233,7 +238,7 @@ hipError_t enqueue_persistent(restore_batch *b, hipStream_t s) {
         const Bucket &bk = b->buckets[i];
         BatchArgs a = args_for(b, &bk, (int)i + 1);
         void *kargs[] = {&a};
-        e = hipLaunchKernel(bk.k.persistent, dim3(bk.grid), dim3(b->tiling.block_size), kargs, 0, s);
+        e = hipLaunchKernel(bk.k.persistent, dim3(bk.grid), dim3(b->tiling.block_size), kargs, bk.lds, s);
         if (e != hipSuccess) return e;
     }
     return launch_batch_reduce(z, s);
@@ -411,7 +416,8 @@ restore_status restore_batch_run(restore_batch *b, int32_t mode, void *stream) {
             int32_t ti = i;
             void *kargs[] = {&a, &ti};
             const int block = b->tiling.block_size;
-            e = hipLaunchKernel(bk->k.per_target, dim3((t.n_chains + block - 1) / block), dim3(block), kargs, 0, s);
+            e = hipLaunchKernel(bk->k.per_target, dim3((t.n_chains + block - 1) / block), dim3(block), kargs, bk->lds,
+                                s);
             if (e != hipSuccess) return hip_fail(e, "per-target launch");
         }
         e = launch_batch_reduce(z, s);

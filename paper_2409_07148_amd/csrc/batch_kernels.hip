@@ -21,9 +21,10 @@ namespace restore {
 // cumulative weights of RESTORE_MAX_COMP components at RESTORE_MAX_DIM.
 constexpr int MU_LDS_FLOATS = RESTORE_MAX_COMP * (MuGmm<RESTORE_MAX_DIM>::STRIDE + 1);
 
-template <int D, int MU>
+template <int D, int MU, bool SPLIT>
 __device__ __forceinline__ void run_item(const BatchArgs &b, const BatchTarget &t, const WorkItem &w,
                                          float *mu_sh) {
+    extern __shared__ __attribute__((aligned(16))) float target_sh[];   // read 16 bytes at a time
     constexpr int NB = NBlocks<D>::value;
     StepArgs a{};
     a.n_chains = t.n_chains;
@@ -39,12 +40,14 @@ __device__ __forceinline__ void run_item(const BatchArgs &b, const BatchTarget &
     a.chain0 = t.chain0;
     a.integrand_p = __builtin_amdgcn_readfirstlane(t.integrand_p);
     a.image = nullptr;
+    a.params = b.params + t.param_offset;
     if (MU == MU_GMM) {
         a.mu_params = b.params + t.mu_offset;
         a.mu_comp = t.mu_comp;
         a.mu_beta = t.mu_beta;
     }
-    const const_fptr P = (const_fptr)(b.params + t.param_offset);
+    const auto P = stage_target<D, false, SPLIT>(a, 0, target_sh);
+    using PT = typename std::remove_cv<decltype(P)>::type;
     // a learned mu is read from the workgroup's LDS copy for this item, as
     // in the single-target kernels (the same arithmetic, the same chains);
     // every thread of the workgroup copies and meets the barrier
@@ -73,7 +76,7 @@ __device__ __forceinline__ void run_item(const BatchArgs &b, const BatchTarget &
     unsigned long long n_t = 0, n_acc = 0, n_kill = 0;
     bool kill = false, accept = false;
     for (int s = 0; s < t.n_steps; ++s) {
-        step_once<D, TGT_FULL, LOC_RWMH, MU, false, const_fptr, false, false, false, false, RT>(
+        step_once<D, TGT_FULL, LOC_RWMH, MU, false, PT, false, false, false, false, RT>(
             a, P, (uint32_t)s, chain, ch, kill, accept, nullptr, MR);
         n_acc += __popcll(__ballot(accept));
         n_kill += __popcll(__ballot(kill));
@@ -87,7 +90,7 @@ __device__ __forceinline__ void run_item(const BatchArgs &b, const BatchTarget &
         n_t += __popcll(live);
         bool k = false, ac = false;
         if (alive) {
-            step_once<D, TGT_FULL, LOC_RWMH, MU, true, const_fptr, false, false, false, false, RT>(
+            step_once<D, TGT_FULL, LOC_RWMH, MU, true, PT, false, false, false, false, RT>(
                 a, P, (uint32_t)s, chain, ch, k, ac, nullptr, MR);
             alive = !k;
         }
@@ -109,11 +112,11 @@ __device__ __forceinline__ void run_item(const BatchArgs &b, const BatchTarget &
     }
 }
 
-template <int DLO, int DHI, int MU>
+template <int DLO, int DHI, int MU, bool SPLIT>
 __device__ __forceinline__ void run_item_dispatch(const BatchArgs &b, const BatchTarget &t, const WorkItem &w,
                                                   float *mu_sh) {
 #define RESTORE_BATCH_CASE(D) \
-    case D: if constexpr (D >= DLO && D <= DHI) run_item<D, MU>(b, t, w, mu_sh); break;
+    case D: if constexpr (D >= DLO && D <= DHI) run_item<D, MU, SPLIT>(b, t, w, mu_sh); break;
     switch (t.d) {
         RESTORE_BATCH_CASE(1) RESTORE_BATCH_CASE(2) RESTORE_BATCH_CASE(3) RESTORE_BATCH_CASE(4)
         RESTORE_BATCH_CASE(5) RESTORE_BATCH_CASE(6) RESTORE_BATCH_CASE(7) RESTORE_BATCH_CASE(8)
@@ -126,25 +129,27 @@ __device__ __forceinline__ void run_item_dispatch(const BatchArgs &b, const Batc
 
 // Persistent: every workgroup pops items until the queue is empty, so every
 // wave reaches the exit once all items are taken.
-template <int DLO, int DHI, int MU>
-__global__ __launch_bounds__(256) void batch_persistent_kernel(BatchArgs b) {
+template <int DLO, int DHI, int MU, bool SPLIT>
+__global__ __launch_bounds__(256, (min_waves(SPLIT, DHI))) void batch_persistent_kernel(BatchArgs b) {
     __shared__ int32_t item_sh;
     __shared__ float mu_sh[MU == MU_GMM ? MU_LDS_FLOATS : 1];
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) item_sh = atomicAdd(b.queue_head, 1);
         __syncthreads();
-        const int32_t item = item_sh;
+        // the same for the whole workgroup, so the item, its target and the
+        // slab's address stay in scalar registers
+        const int32_t item = __builtin_amdgcn_readfirstlane(item_sh);
         if (item >= b.n_items) break;
         const WorkItem w = b.items[item];
         const BatchTarget t = b.targets[w.target];
-        run_item_dispatch<DLO, DHI, MU>(b, t, w, mu_sh);
+        run_item_dispatch<DLO, DHI, MU, SPLIT>(b, t, w, mu_sh);
     }
 }
 
 // One launch per target (the comparison mode): block i takes the i-th tile.
-template <int DLO, int DHI, int MU>
-__global__ __launch_bounds__(256) void batch_target_kernel(BatchArgs b, int32_t target) {
+template <int DLO, int DHI, int MU, bool SPLIT>
+__global__ __launch_bounds__(256, (min_waves(SPLIT, DHI))) void batch_target_kernel(BatchArgs b, int32_t target) {
     __shared__ float mu_sh[MU == MU_GMM ? MU_LDS_FLOATS : 1];
     const BatchTarget t = b.targets[target];
     WorkItem w;
@@ -153,7 +158,7 @@ __global__ __launch_bounds__(256) void batch_target_kernel(BatchArgs b, int32_t 
     w.count = min((int32_t)blockDim.x, t.n_chains - w.first);
     w.pad = 0;
     if (w.count <= 0) return;
-    run_item_dispatch<DLO, DHI, MU>(b, t, w, mu_sh);
+    run_item_dispatch<DLO, DHI, MU, SPLIT>(b, t, w, mu_sh);
 }
 
 __global__ void batch_zero_kernel(BatchArgs b) {
@@ -227,23 +232,27 @@ hipError_t launch_batch_reduce(const BatchArgs &b, hipStream_t s) {
     return hipGetLastError();
 }
 
-BatchKernels find_batch_kernels(int dlo, int dhi, int mu) {
+template <int LO, int HI, int MU>
+static BatchKernels batch_kernels(bool split) {
     BatchKernels k;
-#define RESTORE_BATCH_RANGE(LO, HI)                                                                       \
-    if (dlo == LO && dhi == HI) {                                                                         \
-        k.persistent = mu == MU_GMM ? (const void *)batch_persistent_kernel<LO, HI, MU_GMM>               \
-                                    : (const void *)batch_persistent_kernel<LO, HI, MU_UNIFORM>;          \
-        k.per_target = mu == MU_GMM ? (const void *)batch_target_kernel<LO, HI, MU_GMM>                   \
-                                    : (const void *)batch_target_kernel<LO, HI, MU_UNIFORM>;              \
-        return k;                                                                                         \
-    }
+    k.persistent = split ? (const void *)batch_persistent_kernel<LO, HI, MU, true>
+                         : (const void *)batch_persistent_kernel<LO, HI, MU, false>;
+    k.per_target = split ? (const void *)batch_target_kernel<LO, HI, MU, true>
+                         : (const void *)batch_target_kernel<LO, HI, MU, false>;
+    return k;
+}
+
+BatchKernels find_batch_kernels(int dlo, int dhi, int mu, bool split) {
+#define RESTORE_BATCH_RANGE(LO, HI)     \
+    if (dlo == LO && dhi == HI)         \
+        return mu == MU_GMM ? batch_kernels<LO, HI, MU_GMM>(split) : batch_kernels<LO, HI, MU_UNIFORM>(split);
     RESTORE_BATCH_RANGE(1, 16)
     RESTORE_BATCH_RANGE(1, 4)
     RESTORE_BATCH_RANGE(5, 8)
     RESTORE_BATCH_RANGE(9, 12)
     RESTORE_BATCH_RANGE(13, 16)
 #undef RESTORE_BATCH_RANGE
-    return k;
+    return BatchKernels{};
 }
 
 }  // namespace restore

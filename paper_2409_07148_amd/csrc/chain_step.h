@@ -42,6 +42,25 @@ __device__ __forceinline__ typename ParamPtr<LDS>::type stage_params(const float
     }
 }
 
+// The slab as a kernel reads it: from LDS (LDS), full-covariance mixtures
+// from the scalar cache and LDS (SPLIT, see MixRows), else from the scalar
+// cache.  Every thread of the workgroup calls it.
+template <int D, bool LDS, bool SPLIT>
+__device__ __forceinline__ auto stage_target(const StepArgs &a, int n_floats, float *smem) {
+    if constexpr (SPLIT) {
+        using R = MixRows<D>;
+        const float *src = a.params + 1 + D + R::AT;
+        for (int i = threadIdx.x; i < a.n_comp * R::STRIDE; i += blockDim.x) {
+            const int k = i / R::STRIDE, e = i - k * R::STRIDE;
+            smem[i] = e < R::COUNT ? src[k * comp_stride(TGT_FULL, D) + e] : 0.0f;
+        }
+        __syncthreads();
+        return MixPtr{(const_fptr)a.params, (lds_fptr)smem};
+    } else {
+        return stage_params<LDS>(a.params, n_floats, smem);
+    }
+}
+
 // The learned mu's component blocks and cumulative weights in LDS, for
 // kernels that evaluate log u and sample mu at every step (see MuGmm); the
 // other kernels read them through the scalar cache, with the same
@@ -264,6 +283,9 @@ __device__ __forceinline__ void load_chain(const StepArgs &a, uint32_t c, Chain<
 template <int D, int LOC>
 __device__ __forceinline__ void store_chain(const StepArgs &a, uint32_t c, const Chain<D, LOC> &ch) {
     const int64_t C = a.n_chains;
+    // the addresses anew: kept from load_chain they would hold about 50
+    // registers through the step loop
+    asm volatile("" : "+v"(c));
 #pragma unroll
     for (int i = 0; i < D; ++i) a.x[i * C + c] = ch.x[i];
     if (uses_grad(LOC)) {

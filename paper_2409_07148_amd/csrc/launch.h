@@ -16,6 +16,8 @@ struct KernelSet {
     const void *refresh = nullptr;
     const void *step = nullptr;
     const void *step_lds = nullptr;
+    const void *step_split = nullptr;        // the slab from the scalar cache and LDS (MixRows)
+    const void *step_mh_split = nullptr;
     const void *drain = nullptr;
     const void *drain_lds = nullptr;
     const void *step_binned = nullptr;       // image integrand: binned splats

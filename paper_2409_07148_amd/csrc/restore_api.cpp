@@ -552,11 +552,21 @@ void fill_args(restore_ctx *c) {
     a.image_fx = c->splat.fixed ? at<unsigned long long>(c, c->lay.img_fx) : nullptr;
 }
 
+// Steps read a full-covariance slab half from LDS once there are waves to
+// issue side by side.  Below 2^16 chains a SIMD has at most one: the LDS
+// reads only add to its stream (Metropolis-Hastings steps of 7801 chains at
+// d = 2 and 23 799 at d = 3 run 9% and 11% slower with them; 76 916 chains
+// at d = 6 10% faster, 2^20 at d = 8 18%).  Drains keep to the scalar cache
+// too: all but their first steps run few waves.
+bool split_slab(const restore_ctx *c) {
+    return c->ks.step_split && !c->lds && c->cfg.n_chains >= (1LL << 16);
+}
+
 // Dynamic LDS bytes of a step or drain launch (mu_lds_offset in
 // restore_internal.h): staged target parameters, then the learned mu's
 // component blocks and cumulative weights.
-size_t kernel_lds_bytes(const restore_ctx *c, bool params_lds) {
-    size_t floats = (size_t)mu_lds_offset(params_lds, c->n_params);
+size_t kernel_lds_bytes(const restore_ctx *c, bool params_lds, bool split) {
+    size_t floats = (size_t)mu_lds_offset(params_lds, split, c->n_params, c->v.d, c->v.K);
     if (c->v.mu == MU_GMM) floats += (size_t)c->mu.n_comp * (size_t)(mu_stride(c->v.d) + 1);
     return floats * sizeof(float);
 }
@@ -745,12 +755,15 @@ static restore_status step_impl(restore_ctx *c, int32_t n_steps, int64_t n_recor
     a.rec_chains = n_record;
     int np = c->n_params;
     void *kargs[] = {&a, &np};
-    const size_t shm = kernel_lds_bytes(c, c->lds);
+    const bool split = split_slab(c);
+    const size_t shm = kernel_lds_bytes(c, c->lds, split);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (c->mh) {
         // the MH chain: parameters through the scalar cache, direct splats
-        hipError_t e = hipLaunchKernel(c->ks.step_mh, grid_for(c->cfg.n_chains, c->block), dim3(c->block), kargs,
-                                       kernel_lds_bytes(c, false), s);
+        const bool mh_split = c->ks.step_mh_split && c->cfg.n_chains >= (1LL << 16);
+        hipError_t e = hipLaunchKernel(mh_split ? c->ks.step_mh_split : c->ks.step_mh,
+                                       grid_for(c->cfg.n_chains, c->block), dim3(c->block), kargs,
+                                       kernel_lds_bytes(c, false, mh_split), s);
         if (e != hipSuccess) return hip_fail(e, "MH step launch");
     } else if (c->splat.n_tiles) {
         // tile-stratified: an LDS copy of the workgroup's tile takes the splats
@@ -782,7 +795,7 @@ static restore_status step_impl(restore_ctx *c, int32_t n_steps, int64_t n_recor
             c->pre_n = chunk;
         }
     } else if (!c->splat.n_bins) {
-        const void *fn = c->lds ? c->ks.step_lds : c->ks.step;
+        const void *fn = c->lds ? c->ks.step_lds : split ? c->ks.step_split : c->ks.step;
         hipError_t e = hipLaunchKernel(fn, grid_for(c->cfg.n_chains, c->block), dim3(c->block), kargs, shm, s);
         if (e != hipSuccess) return hip_fail(e, "step launch");
     } else {
@@ -865,7 +878,7 @@ restore_status restore_drain(restore_ctx *c, void *stream) {
     hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, counts, 4);
     const bool tiled = c->splat.n_tiles > 0;
     const void *fn = tiled ? c->ks.drain_tiled : c->lds ? c->ks.drain_lds : c->ks.drain;
-    const size_t shm = tiled ? 0 : kernel_lds_bytes(c, c->lds);
+    const size_t shm = tiled ? 0 : kernel_lds_bytes(c, c->lds, false);
     // chunks of 1, 2, 4, ... steps: survivors are compacted between chunks
     // while many chains retire, and the long tail takes few launches.  A
     // population below 2^16 chains has too few waves to fill the chip, so

@@ -71,12 +71,36 @@ constexpr int PSS_SLAB = 112;
 //   [4 + K * S + K, ...) per component [ m_k (d) | s_k (d) ] for the sampler
 __host__ __device__ constexpr int mu_stride(int d) { return ((1 + 2 * d + 3) / 4) * 4; }
 __host__ __device__ constexpr int mu_slab_floats(int d, int K) { return 4 + K * mu_stride(d) + K + K * 2 * d; }
+// Full-covariance components read half from LDS (MixRows): the first row of
+// the factor that lies there, and the floats of a component's block.
+__host__ __device__ constexpr int mix_first_row(int d) {
+    const int total = 1 + d + d * (d + 1) / 2;
+    int r = d, floats = 0;
+    while (r > 0 && 2 * (floats + r) <= total) {
+        floats += r;
+        --r;
+    }
+    return r;
+}
+__host__ __device__ constexpr int mix_stride(int d) {
+    const int r = mix_first_row(d);
+    return (d * (d + 1) / 2 - r * (r + 1) / 2 + 3) / 4 * 4;
+}
+// Least waves per SIMD to compile such kernels for.  The LDS rows of a
+// component pass through vector registers; left alone the compiler keeps so
+// many in flight that two or three waves fit, too few to issue side by
+// side.  Four waves (128 registers) hold 8-D and 12-D kernels without
+// spills and gain (8-D, 2^20 chains x 128 steps: 3.75 -> 3.4 ms, 12-D
+// 6.0 -> 5.7 ms); from d = 13 they spill (16-D 10 -> 20 ms), and three (168
+// registers) are best.
+__host__ __device__ constexpr int min_waves(bool split, int d) { return !split ? 1 : d <= 12 ? 4 : 3; }
 // Dynamic LDS of the step and drain kernels: the target parameters when
-// they are staged (RESTORE_FLAG_PARAMS_LDS), rounded up to 4 floats, then
-// the learned mu's K * mu_stride(d) component floats and K cumulative
-// weights (slab floats [4, 4 + K (mu_stride(d) + 1))).
-__host__ __device__ constexpr int mu_lds_offset(bool params_lds, int n_param_floats) {
-    return params_lds ? (n_param_floats + 3) / 4 * 4 : 0;
+// they are staged (RESTORE_FLAG_PARAMS_LDS), rounded up to 4 floats, or the
+// LDS rows of K full-covariance components (split), then the learned mu's
+// K * mu_stride(d) component floats and K cumulative weights (slab floats
+// [4, 4 + K (mu_stride(d) + 1))).
+__host__ __device__ constexpr int mu_lds_offset(bool params_lds, bool split, int n_param_floats, int d, int K) {
+    return params_lds ? (n_param_floats + 3) / 4 * 4 : split ? K * mix_stride(d) : 0;
 }
 
 // Fields of the precomputed random inputs of one step (StepRand: t1, e2,

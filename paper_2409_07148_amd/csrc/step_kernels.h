@@ -27,11 +27,11 @@ namespace restore {
 // Steps with regeneration for every chain.  With MH: steps of the
 // Metropolis-Hastings reference chain M^l (no killing, large steps from mu
 // with probability l; see step_once).
-template <int D, int TGT, int LOC, int MU, bool LDS, bool MH = false>
-__global__ __launch_bounds__(256) void step_kernel(StepArgs a, int n_param_floats) {
-    extern __shared__ float smem[];
-    const auto P = stage_params<LDS>(a.params, n_param_floats, smem);
-    const auto MR = stage_mu<D, MU>(a, smem + mu_lds_offset(LDS, n_param_floats));
+template <int D, int TGT, int LOC, int MU, bool LDS, bool MH = false, bool SPLIT = false>
+__global__ __launch_bounds__(256, (min_waves(SPLIT, D))) void step_kernel(StepArgs a, int n_param_floats) {
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    const auto P = stage_target<D, LDS, SPLIT>(a, n_param_floats, smem);
+    const auto MR = stage_mu<D, MU>(a, smem + mu_lds_offset(LDS, SPLIT, n_param_floats, D, a.n_comp));
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= a.n_chains) return;
     Chain<D, LOC> ch;
@@ -309,12 +309,12 @@ __device__ __forceinline__ void splat_flush(const StepArgs &a, uint32_t (*rp)[25
 // past the last chain take part in the barriers only.
 template <int D, int TGT, int LOC, int MU, bool LDS>
 __global__ __launch_bounds__(256) void step_binned_kernel(StepArgs a, int n_param_floats) {
-    extern __shared__ float smem[];
+    extern __shared__ __attribute__((aligned(16))) float smem[];
     __shared__ uint32_t rec_pix[SPLAT_ROWS + 1][256];
     __shared__ float rec_val[SPLAT_ROWS + 1][256];
     __shared__ uint32_t cnt[SPLAT_MAX_BANDS], base[SPLAT_MAX_BANDS];
     const auto P = stage_params<LDS>(a.params, n_param_floats, smem);
-    const auto MR = stage_mu<D, MU>(a, smem + mu_lds_offset(LDS, n_param_floats));
+    const auto MR = stage_mu<D, MU>(a, smem + mu_lds_offset(LDS, false, n_param_floats, D, a.n_comp));
     const int t = threadIdx.x;
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + t;
     const bool active = c < a.n_chains;
@@ -430,10 +430,10 @@ template <int D, int TGT, int LOC, int MU, bool LDS, bool TILED = false>
 __global__ __launch_bounds__(256) void drain_kernel(StepArgs a, int n_param_floats, uint32_t *list_out,
                                                      uint32_t *count_out, uint32_t *count_zero,
                                                      int last_chunk) {
-    extern __shared__ float smem[];
+    extern __shared__ __attribute__((aligned(16))) float smem[];
     const auto P = stage_params<LDS>(a.params, n_param_floats, smem);
     // (tile-stratified runs have the uniform mu)
-    const auto MR = stage_mu<D, TILED ? MU_UNIFORM : MU>(a, smem + mu_lds_offset(LDS, n_param_floats));
+    const auto MR = stage_mu<D, TILED ? MU_UNIFORM : MU>(a, smem + mu_lds_offset(LDS, false, n_param_floats, D, a.n_comp));
     if (blockIdx.x == 0 && threadIdx.x == 0) *count_zero = 0u;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t n_in = a.list ? (int64_t)*a.list_count : a.n_chains;
@@ -548,6 +548,10 @@ static KernelSet make_set() {
     k.step = (const void *)step_kernel<D, TGT, LOC, MU, false>;
     k.step_lds = (const void *)step_kernel<D, TGT, LOC, MU, true>;
     k.step_mh = (const void *)step_kernel<D, TGT, LOC, MU, false, true>;
+    if constexpr (TGT == TGT_FULL) {
+        k.step_split = (const void *)step_kernel<D, TGT, LOC, MU, false, false, true>;
+        k.step_mh_split = (const void *)step_kernel<D, TGT, LOC, MU, false, true, true>;
+    }
     k.drain = (const void *)drain_kernel<D, TGT, LOC, MU, false>;
     k.drain_lds = (const void *)drain_kernel<D, TGT, LOC, MU, true>;
     if constexpr (TGT != TGT_PSS && MU == MU_UNIFORM) {

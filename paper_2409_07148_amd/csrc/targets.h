@@ -25,6 +25,14 @@ typedef const __attribute__((address_space(4))) float *const_fptr;
 // An LDS copy of read-only parameters (per-lane indexed reads are ds_reads).
 typedef const __attribute__((address_space(3))) float *lds_fptr;
 
+// A packed full-covariance slab read both ways at once: the scalar cache,
+// and an LDS copy of the last rows of every component's factor (see
+// GmmFull; one 16-byte aligned block of MixRows<D>::STRIDE floats each).
+struct MixPtr {
+    const_fptr P;
+    lds_fptr L;
+};
+
 // Components per log-sum-exp block: four for values alone, two when the
 // gradient needs each component's vector until the block's weights are
 // known (fewer live registers), and fewer while the block's parameters
@@ -132,6 +140,52 @@ struct GmmIsoInflow {
     }
 };
 
+// Which part of a full-covariance component the step kernels read from LDS.
+// What bounds the density is issue.  Two waves of a SIMD issue FP32
+// instructions side by side (2.05 cycles each) only while at most one of
+// the two reads a scalar register: with a scalar operand in each a SIMD
+// issues one per 4.1 cycles.  An LDS broadcast read delivers a parameter
+// to a vector register in 4.2 cycles of the SIMD's share, beside the VALU.
+// So half the parameters take each way (48 parameters from the scalar cache
+// alone cost 218 cycles a wave, from LDS alone 203, half and half 143;
+// between a third and two thirds the choice does not matter).  The last
+// rows are one contiguous run: as many whole rows as fit in half the floats.
+template <int D>
+struct MixRows {
+    static constexpr int FIRST = mix_first_row(D);            // first row read from LDS
+    static constexpr int AT = FIRST * (FIRST + 1) / 2;        // its index in the packed triangle
+    static constexpr int COUNT = D * (D + 1) / 2 - AT;        // floats per component
+    static constexpr int STRIDE = mix_stride(D);
+};
+
+// One component's factor entries W[i (i + 1) / 2 + j].
+template <int D, class PT>
+struct FactorOf {
+    const PT W;
+    __device__ __forceinline__ FactorOf(PT P, int k) : W(P + k * comp_stride(TGT_FULL, D) + 1 + D) {}
+    __device__ __forceinline__ float operator[](int i) const { return W[i]; }
+};
+template <int D>
+struct FactorOf<D, MixPtr> {
+    using R = MixRows<D>;
+    const const_fptr W;
+    float v[R::STRIDE];
+    __device__ __forceinline__ FactorOf(MixPtr P, int k) : W(P.P + k * comp_stride(TGT_FULL, D) + 1 + D) {
+        typedef float v4f __attribute__((ext_vector_type(4)));
+        typedef const __attribute__((address_space(3))) v4f *lds_v4ptr;
+        const auto q = (lds_v4ptr)(P.L + k * R::STRIDE);
+#pragma unroll
+        for (int i = 0; i < R::STRIDE / 4; ++i) {
+            const v4f t = q[i];
+            v[4 * i] = t.x; v[4 * i + 1] = t.y; v[4 * i + 2] = t.z; v[4 * i + 3] = t.w;
+        }
+    }
+    __device__ __forceinline__ float operator[](int i) const { return i >= R::AT ? v[i >= R::AT ? i - R::AT : 0] : W[i]; }
+};
+template <class PT>
+__device__ __forceinline__ PT scalar_part(PT P) { return P; }
+__device__ __forceinline__ const_fptr scalar_part(MixPtr P) { return P.P; }
+
 // Full-covariance Gaussian mixture with scaled whitening factors
 // W_k = sqrt(log2 e / 2) L_k^-1 (S_k = L_k L_k^T, W_k lower triangular),
 // terms in base 2:
@@ -147,8 +201,8 @@ struct GmmFull {
         float a[B], v[B][D];
 #pragma unroll
         for (int b = 0; b < B; ++b) {
-            const auto pk = P + (k0 + b) * STRIDE;
-            const auto W = pk + 1 + D;
+            const auto pk = scalar_part(P) + (k0 + b) * STRIDE;
+            const FactorOf<D, PT> W(P, k0 + b);
             float dx[D];
 #pragma unroll
             for (int i = 0; i < D; ++i) dx[i] = y[i] - pk[1 + i];
@@ -172,7 +226,7 @@ struct GmmFull {
             for (int j = 0; j < D; ++j) G[j] *= sc;
 #pragma unroll
             for (int b = 0; b < B; ++b) {
-                const auto W = P + (k0 + b) * STRIDE + 1 + D;
+                const FactorOf<D, PT> W(P, k0 + b);
 #pragma unroll
                 for (int j = 0; j < D; ++j) {
                     float u = 0.0f;

@@ -46,7 +46,7 @@ __device__ __forceinline__ void run_item(const BatchArgs &b, const BatchTarget &
         a.mu_comp = t.mu_comp;
         a.mu_beta = t.mu_beta;
     }
-    const auto P = stage_target<D, false, SPLIT>(a, 0, target_sh);
+    const auto P = stage_target<D, false, SPLIT && D >= MIX_MIN_DIM>(a, 0, target_sh);
     using PT = typename std::remove_cv<decltype(P)>::type;
     // a learned mu is read from the workgroup's LDS copy for this item, as
     // in the single-target kernels (the same arithmetic, the same chains);

@@ -111,7 +111,11 @@ __device__ __forceinline__ float log_u_state(const StepArgs &a, PT P, const floa
     const float lu = log_mu<D, MU>(a, y, R);
     if constexpr (LOC == LOC_RWU && TGT == TGT_ISO) {
         if (lp == -INFINITY) return 0.0f;
-        const float lq = GmmIsoInflow<D>::log_inflow(P, a.n_comp, y) - a.log_c;
+        float lq;
+        if constexpr (std::is_same<typename std::remove_cv<PT>::type, RowPtr>::value)
+            lq = GmmIsoInflow<D>::log_inflow_row(P, a.n_comp, y) - a.log_c;
+        else
+            lq = GmmIsoInflow<D>::log_inflow(P, a.n_comp, y) - a.log_c;
         const float M = fmaxf(lu, lq);
         const float v = expf(lu - M) + expf(lq - M) - expf((lp - a.log_c) - M);
         return v >= 0.0f ? M + logf(v) : NAN;
@@ -280,12 +284,13 @@ __device__ __forceinline__ void load_chain(const StepArgs &a, uint32_t c, Chain<
                       : 0;
 }
 
-template <int D, int LOC>
+// ANEW: the addresses are formed anew; kept from load_chain they would hold
+// about 50 registers through the step loop, which kernels with many waves to
+// run do not have to spare.
+template <bool ANEW = false, int D, int LOC>
 __device__ __forceinline__ void store_chain(const StepArgs &a, uint32_t c, const Chain<D, LOC> &ch) {
     const int64_t C = a.n_chains;
-    // the addresses anew: kept from load_chain they would hold about 50
-    // registers through the step loop
-    asm volatile("" : "+v"(c));
+    if (ANEW) asm volatile("" : "+v"(c));
 #pragma unroll
     for (int i = 0; i < D; ++i) a.x[i * C + c] = ch.x[i];
     if (uses_grad(LOC)) {

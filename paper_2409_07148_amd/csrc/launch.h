@@ -31,6 +31,10 @@ struct KernelSet {
     const void *rand_prepass = nullptr;
     const void *step_pre = nullptr;    // also runs the next chunk's pre-pass
     const void *drain_pre = nullptr;
+    // the same with `lanes` lanes a chain
+    int lanes = 1;
+    const void *step_lanes = nullptr;
+    const void *drain_lanes = nullptr;
 };
 
 // Binned splats of one step launch into the image: per-band LDS

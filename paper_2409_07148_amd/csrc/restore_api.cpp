@@ -116,6 +116,9 @@ SplatPlan splat_plan(const restore_config *cfg, int tgt) {
     return sp;
 }
 
+// Longest list that a drain runs with several lanes a chain: two waves a SIMD.
+constexpr int64_t DRAIN_WIDE_MAX = 2048LL * 64 / FULL_LANES;
+
 constexpr int64_t RAND_HALF_BYTES = 32LL << 20;
 
 RandPlan rand_plan(const restore_config *cfg, int tgt, int d, int mu) {
@@ -473,6 +476,7 @@ struct restore_ctx {
     int n_params = 0;
     int block = 256;
     bool lds = false;
+    int lanes = 1;              // lanes a chain of the pre-pass kernels
     bool drained = false;
     bool mh = false;            // c_tilde = 0: the MH chain M^l
     int32_t steps_taken = 0;
@@ -569,6 +573,12 @@ size_t kernel_lds_bytes(const restore_ctx *c, bool params_lds, bool split) {
     size_t floats = (size_t)mu_lds_offset(params_lds, split, c->n_params, c->v.d, c->v.K);
     if (c->v.mu == MU_GMM) floats += (size_t)c->mu.n_comp * (size_t)(mu_stride(c->v.d) + 1);
     return floats * sizeof(float);
+}
+
+// The same of the pre-pass kernels: with several lanes a chain a
+// full-covariance slab.
+size_t lanes_lds_bytes(const restore_ctx *c) {
+    return c->lanes > 1 && c->v.tgt == TGT_FULL ? sizeof(float) * (size_t)quad_slab_floats(c->v.d, c->v.K) : 0;
 }
 
 // Half h of the pre-pass buffer.
@@ -698,6 +708,8 @@ restore_status restore_init(restore_ctx **out, const restore_target *target, con
     c->mu = *mu;
     c->splat = sp;
     c->rand = ks.step_pre ? rp : RandPlan{};
+    // lanes a chain while that leaves at most two waves a SIMD
+    if (ks.step_lanes && cfg->n_chains * ks.lanes <= 2048LL * 64) c->lanes = ks.lanes;
     fill_args(c);
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -776,8 +788,9 @@ static restore_status step_impl(restore_ctx *c, int32_t n_steps, int64_t n_recor
         // from one half of the pre-pass buffer while extra workgroups of the
         // same launch fill the other half with the next chunk
         int chunk = c->rand.chunk;
-        const int64_t step_blocks = (c->cfg.n_chains + c->block - 1) / c->block;
-        const int64_t gen_blocks = step_blocks * ((chunk + PRE_GEN_STEPS - 1) / PRE_GEN_STEPS);
+        const int64_t step_blocks = (c->cfg.n_chains * c->lanes + c->block - 1) / c->block;
+        const int64_t gen_blocks = (c->cfg.n_chains + c->block - 1) / c->block *
+                                   ((chunk + PRE_GEN_STEPS - 1) / PRE_GEN_STEPS);
         for (int32_t done = 0; done < n_steps; done += chunk) {
             const int64_t s_first = c->steps_taken + done;
             a.s0 = (uint32_t)s_first;
@@ -787,8 +800,9 @@ static restore_status step_impl(restore_ctx *c, int32_t n_steps, int64_t n_recor
             const float *cur = rand_half(c, c->pre_half);
             PreGen g{rand_half(c, 1 - c->pre_half), (uint32_t)(s_first + a.n_steps), chunk, (int32_t)step_blocks};
             void *sargs[] = {&a, &cur, &chunk, &g};
-            hipError_t e = hipLaunchKernel(c->ks.step_pre, dim3((unsigned)(step_blocks + gen_blocks)),
-                                           dim3(c->block), sargs, 0, s);
+            hipError_t e = hipLaunchKernel(c->lanes > 1 ? c->ks.step_lanes : c->ks.step_pre,
+                                           dim3((unsigned)(step_blocks + gen_blocks)), dim3(c->block), sargs,
+                                           lanes_lds_bytes(c), s);
             if (e != hipSuccess) return hip_fail(e, "step launch");
             c->pre_half = 1 - c->pre_half;
             c->pre_s0 = s_first + a.n_steps;
@@ -867,8 +881,9 @@ restore_status restore_drain(restore_ctx *c, void *stream) {
         const float *cur = rand_half(c, c->pre_half);
         int chunk = c->rand.chunk, np = n_pre;
         void *kargs[] = {&a, &cur, &chunk, &np};
-        hipError_t e = hipLaunchKernel(c->ks.drain_pre, grid_for(c->cfg.n_chains, c->block), dim3(c->block), kargs,
-                                       0, s);
+        hipError_t e = hipLaunchKernel(c->lanes > 1 ? c->ks.drain_lanes : c->ks.drain_pre,
+                                       grid_for(c->cfg.n_chains * c->lanes, c->block), dim3(c->block), kargs,
+                                       lanes_lds_bytes(c), s);
         if (e != hipSuccess) return hip_fail(e, "drain launch");
         c->drained = true;
         return RESTORE_OK;
@@ -878,7 +893,12 @@ restore_status restore_drain(restore_ctx *c, void *stream) {
     hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, counts, 4);
     const bool tiled = c->splat.n_tiles > 0;
     const void *fn = tiled ? c->ks.drain_tiled : c->lds ? c->ks.drain_lds : c->ks.drain;
-    const size_t shm = tiled ? 0 : kernel_lds_bytes(c, c->lds, false);
+    const bool wide = drains_wide(c->v.tgt, c->v.mu) && !c->lds;
+    const size_t shm = tiled ? 0
+                       : wide ? sizeof(float) * (size_t)quad_slab_floats(c->v.d, c->v.K)
+                              : kernel_lds_bytes(c, c->lds, false);
+    // (the grid has a lane for every chain)
+    const int wide_max = wide ? (int)std::min<int64_t>(DRAIN_WIDE_MAX, c->cfg.n_chains / FULL_LANES) : 0;
     // chunks of 1, 2, 4, ... steps: survivors are compacted between chunks
     // while many chains retire, and the long tail takes few launches.  A
     // population below 2^16 chains has too few waves to fill the chip, so
@@ -900,7 +920,7 @@ restore_status restore_drain(restore_ctx *c, void *stream) {
         uint32_t *list_out = lists[j % 2];
         uint32_t *count_out = counts + ((j + 1) % 3);
         uint32_t *count_zero = counts + ((j + 2) % 3);
-        void *kargs[] = {&a, &np, &list_out, &count_out, &count_zero, (void *)&last};
+        void *kargs[] = {&a, &np, &list_out, &count_out, &count_zero, (void *)&last, (void *)&wide_max};
         hipError_t e = hipLaunchKernel(fn, grid_for(c->cfg.n_chains, c->block), dim3(c->block), kargs, shm, s);
         if (e != hipSuccess) return hip_fail(e, "drain launch");
         s0 += (uint32_t)L;

@@ -71,8 +71,20 @@ constexpr int PSS_SLAB = 112;
 //   [4 + K * S + K, ...) per component [ m_k (d) | s_k (d) ] for the sampler
 __host__ __device__ constexpr int mu_stride(int d) { return ((1 + 2 * d + 3) / 4) * 4; }
 __host__ __device__ constexpr int mu_slab_floats(int d, int K) { return 4 + K * mu_stride(d) + K + K * 2 * d; }
-// Full-covariance components read half from LDS (MixRows): the first row of
+// Lanes a chain of the kernels that spread chains over lanes (targets.h):
+// full-covariance mixtures; the unadjusted jump process.
+constexpr int FULL_LANES = 4;
+constexpr int INFLOW_LANES = 16;
+// Floats of a full-covariance slab in LDS with four lanes a chain: whole
+// passes of four components.
+__host__ __device__ constexpr int quad_slab_floats(int d, int K) { return (K + 3) / 4 * 4 * comp_stride(TGT_FULL, d); }
+// the drain kernels that take it for short lists
+__host__ __device__ constexpr bool drains_wide(int tgt, int mu) { return tgt == TGT_FULL && mu == MU_UNIFORM; }
+// Full-covariance components read half from LDS (MixRows), from this
+// dimension on (at d = 3 a component's five floats fill two 16-byte reads:
+// 69 610 chains ran 3.5% slower); the first row of
 // the factor that lies there, and the floats of a component's block.
+constexpr int MIX_MIN_DIM = 4;
 __host__ __device__ constexpr int mix_first_row(int d) {
     const int total = 1 + d + d * (d + 1) / 2;
     int r = d, floats = 0;
@@ -115,7 +127,7 @@ struct PreGen {
     float *out;           // the buffer half it fills
     uint32_t s0;          // first step it draws
     int32_t n_steps;      // steps it draws (<= chunk; 0: none)
-    int32_t step_blocks;  // workgroups of the step launch proper
+    int32_t step_blocks;  // workgroups of the step launch proper (its lanes a chain may differ)
 };
 
 // Per-launch arguments of the step kernels.

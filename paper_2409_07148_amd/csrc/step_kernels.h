@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256, (min_waves(SPLIT, D))) void step_kernel(StepAr
     ch.status = (ch.status & ~(ST_LAST_KILL | ST_LAST_ACCEPT)) | (kill ? ST_LAST_KILL : 0u) |
                 (accept ? ST_LAST_ACCEPT : 0u);
     if (TGT == TGT_PSS && a.image) flush_splat(a, ch.splat_pix, ch.splat_acc, ch.splat_fx);
-    store_chain(a, (uint32_t)c, ch);
+    store_chain<SPLIT>(a, (uint32_t)c, ch);
     const unsigned long long lanes = __popcll(__ballot(1));
     add_counters(a.counters, lanes * (unsigned long long)a.n_steps, n_acc, n_kill, n_large, n_large_acc);
 }
@@ -146,21 +146,45 @@ struct PreFetch {
     }
 };
 
+// The slab as the kernels of small populations read it: spread over G lanes
+// a chain (targets.h), a full-covariance slab from LDS.  Every thread of the
+// workgroup calls it.
+template <int D, int TGT, int G>
+__device__ __forceinline__ auto lane_target(const StepArgs &a, float *smem) {
+    if constexpr (G == 1) {
+        (void)smem;
+        return (const_fptr)a.params;
+    } else if constexpr (TGT == TGT_FULL) {
+        static_assert(G == FULL_LANES, "four lanes a chain");
+        constexpr int S = comp_stride(TGT_FULL, D);
+        const int n = a.n_comp * S, all = quad_slab_floats(D, a.n_comp);
+        for (int i = threadIdx.x; i < all; i += blockDim.x)
+            smem[i] = i < n ? a.params[i] : i % S == 0 ? -0x1.fffffep127f : 0.0f;
+        __syncthreads();
+        return QuadPtr{(lds_fptr)smem, (int)(threadIdx.x % G)};
+    } else {
+        static_assert(G == INFLOW_LANES, "sixteen lanes a chain");
+        return RowPtr((const_fptr)a.params, D, a.n_comp, (int)(threadIdx.x % G));
+    }
+}
+
 // Steps with regeneration whose random inputs come from the pre-pass (a
 // chunk of at most `chunk` steps; step it of the launch reads field f at
 // pre[(f chunk + it) C + c]).  Two register buffers of PF steps alternate:
 // one is loaded while the other's steps run.  The same chains as
 // step_kernel, bit for bit.
-template <int D, int TGT, int LOC>
-__global__ __launch_bounds__(256) void step_pre_kernel(StepArgs a, const float *pre, int chunk, PreGen g) {
+template <int D, int TGT, int LOC, int G>
+__global__ __launch_bounds__(256, G > 1 ? 2 : 1) void step_pre_kernel(StepArgs a, const float *pre, int chunk, PreGen g) {
     if ((int64_t)blockIdx.x >= g.step_blocks) {
         pregen_block<D>(a, g, chunk);
         return;
     }
     using PFT = PreFetch<D>;
     constexpr int PF = PFT::PF;
-    const const_fptr P = (const_fptr)a.params;
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    auto P = lane_target<D, TGT, G>(a, smem);
+    using PT = decltype(P);
+    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
     if (c >= a.n_chains) return;
     Chain<D, LOC> ch;
     load_chain(a, (uint32_t)c, ch);
@@ -173,7 +197,7 @@ __global__ __launch_bounds__(256) void step_pre_kernel(StepArgs a, const float *
 #pragma unroll
         for (int j = 0; j < PF; ++j) {
             if (it0 + j < a.n_steps) {
-                step_once<D, TGT, LOC, MU_UNIFORM, false, const_fptr, false, false, false, true>(
+                step_once<D, TGT, LOC, MU_UNIFORM, false, PT, false, false, false, true>(
                     a, P, a.s0 + (uint32_t)(it0 + j), (uint32_t)c, ch, kill, accept, &r[j]);
                 n_acc += __popcll(__ballot(accept));
                 n_kill += __popcll(__ballot(kill));
@@ -190,21 +214,23 @@ __global__ __launch_bounds__(256) void step_pre_kernel(StepArgs a, const float *
     }
     ch.status = (ch.status & ~(ST_LAST_KILL | ST_LAST_ACCEPT)) | (kill ? ST_LAST_KILL : 0u) |
                 (accept ? ST_LAST_ACCEPT : 0u);
-    store_chain(a, (uint32_t)c, ch);
-    const unsigned long long lanes = __popcll(__ballot(1));
-    add_counters(a.counters, lanes * (unsigned long long)a.n_steps, n_acc, n_kill);
+    if (threadIdx.x % G == 0) store_chain(a, (uint32_t)c, ch);
+    const unsigned long long lanes = __popcll(__ballot(1)) / G;
+    add_counters(a.counters, lanes * (unsigned long long)a.n_steps, n_acc / G, n_kill / G);
 }
 
 // The drain of a small population in one launch (no chain list): the first
 // n_pre steps take their random inputs from the pre-pass, later ones draw
 // them inline.  A wave ends when its last lane's tour is killed; survivors
 // of all a.n_steps steps are censored.  The same chains as drain_kernel.
-template <int D, int TGT, int LOC>
-__global__ __launch_bounds__(256) void drain_pre_kernel(StepArgs a, const float *pre, int chunk, int n_pre) {
+template <int D, int TGT, int LOC, int G>
+__global__ __launch_bounds__(256, G > 1 ? 2 : 1) void drain_pre_kernel(StepArgs a, const float *pre, int chunk, int n_pre) {
     using PFT = PreFetch<D>;
     constexpr int PF = PFT::PF;
-    const const_fptr P = (const_fptr)a.params;
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    auto P = lane_target<D, TGT, G>(a, smem);
+    using PT = decltype(P);
+    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
     if (c >= a.n_chains) return;
     Chain<D, LOC> ch;
     load_chain(a, (uint32_t)c, ch);
@@ -219,10 +245,10 @@ __global__ __launch_bounds__(256) void drain_pre_kernel(StepArgs a, const float 
         bool kill = false, accept = false;
         if (alive) {
             if (r)
-                step_once<D, TGT, LOC, MU_UNIFORM, true, const_fptr, false, false, false, true>(
+                step_once<D, TGT, LOC, MU_UNIFORM, true, PT, false, false, false, true>(
                     a, P, a.s0 + (uint32_t)it, (uint32_t)c, ch, kill, accept, r);
             else
-                step_once<D, TGT, LOC, MU_UNIFORM, true, const_fptr>(a, P, a.s0 + (uint32_t)it, (uint32_t)c, ch,
+                step_once<D, TGT, LOC, MU_UNIFORM, true, PT>(a, P, a.s0 + (uint32_t)it, (uint32_t)c, ch,
                                                                      kill, accept);
             stepped = true;
             kill_last = kill;
@@ -259,8 +285,8 @@ __global__ __launch_bounds__(256) void drain_pre_kernel(StepArgs a, const float 
                     (kill_last ? ST_LAST_KILL : 0u) | (acc_last ? ST_LAST_ACCEPT : 0u);
     }
     if (alive) ch.status |= ST_CENSORED;
-    store_chain(a, (uint32_t)c, ch);
-    add_counters(a.counters, n_t, n_acc, n_kill);
+    if (threadIdx.x % G == 0) store_chain(a, (uint32_t)c, ch);
+    add_counters(a.counters, n_t / G, n_acc / G, n_kill / G);
 }
 
 // Binning of the records staged in LDS: rows [0, rows) of this thread's
@@ -422,22 +448,17 @@ __global__ __launch_bounds__(256) void step_tiled_kernel(StepArgs a, int n_param
     }
 }
 
-// Drain: the chains of the input list run on without regeneration until
-// their tour in flight is killed.  Survivors of this chunk are compacted
-// into the output list with one ballot and one atomic per wave; on the last
-// chunk they are marked censored instead.
-template <int D, int TGT, int LOC, int MU, bool LDS, bool TILED = false>
-__global__ __launch_bounds__(256) void drain_kernel(StepArgs a, int n_param_floats, uint32_t *list_out,
-                                                     uint32_t *count_out, uint32_t *count_zero,
-                                                     int last_chunk) {
-    extern __shared__ __attribute__((aligned(16))) float smem[];
-    const auto P = stage_params<LDS>(a.params, n_param_floats, smem);
-    // (tile-stratified runs have the uniform mu)
-    const auto MR = stage_mu<D, TILED ? MU_UNIFORM : MU>(a, smem + mu_lds_offset(LDS, false, n_param_floats, D, a.n_comp));
-    if (blockIdx.x == 0 && threadIdx.x == 0) *count_zero = 0u;
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t n_in = a.list ? (int64_t)*a.list_count : a.n_chains;
+// Drain steps of the chain at place `at` of the input list of n_in chains
+// (a.list; all chains in order without one), G lanes a chain: until its tour
+// in flight is killed, without regeneration.  Survivors of this chunk are
+// compacted into the output list with one ballot and one atomic per wave;
+// on the last chunk they are marked censored instead.
+template <int D, int TGT, int LOC, int MU, bool TILED, int G, class PT, class RT>
+__device__ __forceinline__ void drain_chain(const StepArgs &a, PT P, RT MR, int64_t at, int64_t n_in,
+                                            uint32_t *list_out, uint32_t *count_out, int last_chunk) {
+    const int64_t idx = at / G;
     if (idx >= n_in) return;
+    const bool first = at % G == 0;
     const uint32_t c = a.list ? a.list[idx] : (uint32_t)idx;
     Chain<D, LOC> ch;
     load_chain(a, c, ch);
@@ -450,7 +471,7 @@ __global__ __launch_bounds__(256) void drain_kernel(StepArgs a, int n_param_floa
         n_t += __popcll(live);
         bool kill = false, accept = false;
         if (alive) {
-            step_once<D, TGT, LOC, MU, true, decltype(P), false, false, TILED, false, decltype(MR)>(
+            step_once<D, TGT, LOC, MU, true, PT, false, false, TILED, false, RT>(
                 a, P, a.s0 + (uint32_t)it, c, ch, kill, accept, nullptr, MR);
             stepped = true;
             kill_last = kill;
@@ -468,21 +489,49 @@ __global__ __launch_bounds__(256) void drain_kernel(StepArgs a, int n_param_floa
     if (TGT == TGT_PSS && a.image)
         flush_splat(a, TILED ? tile_to_image(a, ch.tpx0, ch.tpy0, ch.img_base, ch.splat_pix) : ch.splat_pix,
                     ch.splat_acc, ch.splat_fx);
-    store_chain(a, c, ch);
-    add_counters(a.counters, n_t, n_acc, n_kill);
+    if (first) store_chain(a, c, ch);
+    add_counters(a.counters, n_t / G, n_acc / G, n_kill / G);
     if (!last_chunk) {
-        const unsigned long long keep = __ballot(alive);
+        const unsigned long long keep = __ballot(alive && first);
         if (keep) {
             const int leader = __ffsll((long long)keep) - 1;
             uint32_t base = 0;
             if (lane_id() == leader) base = atomicAdd(count_out, (uint32_t)__popcll(keep));
             base = __shfl(base, leader);
-            if (alive) {
+            if (alive && first) {
                 const uint32_t below = (uint32_t)__popcll(keep & ((1ull << lane_id()) - 1ull));
                 list_out[base + below] = c;
             }
         }
     }
+}
+
+// Drain.  The grid covers every chain; once the list is short enough
+// (wide_max chains: a wave or two a SIMD) a full-covariance chain takes
+// FULL_LANES lanes, as what is left of the drain is the length of its
+// longest tours.
+template <int D, int TGT, int LOC, int MU, bool LDS, bool TILED = false>
+__global__ __launch_bounds__(256) void drain_kernel(StepArgs a, int n_param_floats, uint32_t *list_out,
+                                                     uint32_t *count_out, uint32_t *count_zero,
+                                                     int last_chunk, int wide_max) {
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *count_zero = 0u;
+    const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t n_in = a.list ? (int64_t)*a.list_count : a.n_chains;
+    if constexpr (drains_wide(TGT, MU) && !LDS) {
+        if (n_in <= wide_max) {
+            if ((int64_t)blockIdx.x * blockDim.x >= n_in * FULL_LANES) return;
+            const auto Q = lane_target<D, TGT, FULL_LANES>(a, smem);
+            drain_chain<D, TGT, LOC, MU, TILED, FULL_LANES>(a, Q, (const_fptr) nullptr, at, n_in, list_out, count_out,
+                                                            last_chunk);
+            return;
+        }
+    }
+    const auto P = stage_params<LDS>(a.params, n_param_floats, smem);
+    // (tile-stratified runs have the uniform mu)
+    const auto MR = stage_mu<D, TILED ? MU_UNIFORM : MU>(a, smem + mu_lds_offset(LDS, false, n_param_floats, D, a.n_comp));
+    drain_chain<D, TGT, LOC, MU, TILED, 1, decltype(P), decltype(MR)>(a, P, MR, at, n_in, list_out, count_out,
+                                                                      last_chunk);
 }
 
 // x_0 ~ mu (purpose INIT, step 0), cached log p / log u / grad, zero sums.
@@ -548,7 +597,7 @@ static KernelSet make_set() {
     k.step = (const void *)step_kernel<D, TGT, LOC, MU, false>;
     k.step_lds = (const void *)step_kernel<D, TGT, LOC, MU, true>;
     k.step_mh = (const void *)step_kernel<D, TGT, LOC, MU, false, true>;
-    if constexpr (TGT == TGT_FULL) {
+    if constexpr (TGT == TGT_FULL && D >= MIX_MIN_DIM) {
         k.step_split = (const void *)step_kernel<D, TGT, LOC, MU, false, false, true>;
         k.step_mh_split = (const void *)step_kernel<D, TGT, LOC, MU, false, true, true>;
     }
@@ -556,8 +605,14 @@ static KernelSet make_set() {
     k.drain_lds = (const void *)drain_kernel<D, TGT, LOC, MU, true>;
     if constexpr (TGT != TGT_PSS && MU == MU_UNIFORM) {
         k.rand_prepass = (const void *)rand_prepass_kernel<D>;
-        k.step_pre = (const void *)step_pre_kernel<D, TGT, LOC>;
-        k.drain_pre = (const void *)drain_pre_kernel<D, TGT, LOC>;
+        k.step_pre = (const void *)step_pre_kernel<D, TGT, LOC, 1>;
+        k.drain_pre = (const void *)drain_pre_kernel<D, TGT, LOC, 1>;
+        if constexpr (TGT == TGT_FULL || (LOC == LOC_RWU && D <= 2)) {
+            constexpr int G = TGT == TGT_FULL ? FULL_LANES : INFLOW_LANES;
+            k.lanes = G;
+            k.step_lanes = (const void *)step_pre_kernel<D, TGT, LOC, G>;
+            k.drain_lanes = (const void *)drain_pre_kernel<D, TGT, LOC, G>;
+        }
     }
     if constexpr (TGT == TGT_PSS) {
         k.step_binned = (const void *)step_binned_kernel<D, TGT, LOC, MU, false>;

@@ -33,6 +33,50 @@ struct MixPtr {
     lds_fptr L;
 };
 
+// Chains spread over several lanes (small populations and the tails of
+// drains, where a SIMD has a wave or two and a step costs its instruction
+// stream): every lane of a group of G holds the whole chain and computes
+// the same step, and the group shares out the density's components.  The
+// lanes of a group take every branch together.
+// A full-covariance slab in LDS, four lanes a chain:
+struct QuadPtr {
+    lds_fptr L;
+    int role;   // the lane within its chain's four
+};
+// The isotropic mixture of the unadjusted jump process, sixteen lanes a
+// chain (see GmmIsoInflow):
+struct RowPtr {
+    const_fptr P;
+    int role;   // the lane within its chain's sixteen
+    // the first pass's component of this lane: means and inflow parameters
+    float m[2], c, ivar, alpha, beta;
+    __device__ __forceinline__ RowPtr(const_fptr slab, int d, int K, int lane) : P(slab), role(lane) { load(d, K, 0); }
+    __device__ __forceinline__ void load(int d, int K, int k0) {
+        const int S = comp_stride(TGT_ISO, d), k = min(k0 + role / (2 * d), K - 1);
+        m[0] = P[k * S + 1];
+        m[1] = d == 2 ? P[k * S + 2] : 0.0f;
+        const const_fptr q = P + K * S + k * INFLOW_STRIDE;
+        c = q[0]; ivar = q[1]; alpha = q[2]; beta = q[3];
+    }
+};
+// lane R's x of each group of four, and of each row of sixteen
+template <int R>
+__device__ __forceinline__ float quad_bcast(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), R * 0x55, 0xf, 0xf, true));
+}
+template <int R>
+__device__ __forceinline__ float row_bcast(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + R, 0xf, 0xf, true));
+}
+// f(0), .., f(N - 1) with compile-time indices
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
 // Components per log-sum-exp block: four for values alone, two when the
 // gradient needs each component's vector until the block's weights are
 // known (fewer live registers), and fewer while the block's parameters
@@ -112,8 +156,46 @@ struct GmmIso {
 // c_i = m_i + alpha (y_i - m_i) with 1 / sqrt(2 var) = beta:
 //   (erf(beta (1 - c_i)) + erf(beta c_i)) / 2.
 // The parameters (INFLOW_STRIDE per component) follow the K components.
+//
+// With sixteen lanes a chain and d <= 2, each lane takes one error function:
+// 2d lanes a component, 8 / d components at a time; the lanes of a component
+// share its truncation factors (a sum and a product of two, so the same bits
+// in either order) and its logarithm, and every lane adds the components up
+// in order.
 template <int D>
 struct GmmIsoInflow {
+    __device__ __forceinline__ static float log_inflow_row(RowPtr P, int K, const float y[D]) {
+        static_assert(D <= 2, "one or two coordinates");
+        constexpr int PER = 8 / D;   // components per pass
+        const int i = D == 2 ? (P.role >> 1) & 1 : 0;
+        const bool lower = (P.role & 1) != 0;
+        float M = -INFINITY, S = 0.0f;
+        for (int k0 = 0; k0 < K; k0 += PER) {
+            if (k0 > 0) P.load(D, K, k0);
+            float q = 0.0f, c = 0.0f;
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                const float dx = y[j] - P.m[j];
+                q = fmaf(dx, dx, q);
+                const float cj = fmaf(P.alpha, dx, P.m[j]);
+                c = j == i ? cj : c;
+            }
+            const float e = erff(P.beta * (lower ? c : 1.0f - c));
+            const float other = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(e), 0xb1, 0xf, 0xf, true));
+            float mass = 0.5f * (e + other);
+            if (D == 2)
+                mass *= __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(mass), 0x4e, 0xf, 0xf, true));
+            const float ak = fmaf(-0.5f * P.ivar, q, P.c) + logf(mass);
+            static_for<0, PER>([&](auto j) {
+                if (k0 + j < K) {
+                    float sc, w;
+                    lse_push(M, S, row_bcast<j * 2 * D>(ak), sc, w);
+                }
+            });
+        }
+        return M + logf(S);
+    }
+
     template <class PT>
     __device__ __forceinline__ static float log_inflow(PT P, int K, const float y[D]) {
         const auto A = P + K * GmmIso<D>::STRIDE;
@@ -238,22 +320,113 @@ struct GmmFull {
         }
     }
 
-    template <bool GRAD, int BMAX = 4, class PT>
-    __device__ __forceinline__ static float eval(PT P, int K, const float y[D], float g[D], bool want) {
+    // Four components at a time, one per lane of the chain's four: each lane
+    // forms its component's term and W^T v, then all four run the same
+    // log-sum-exp blocks and gradient sums over the broadcast results, in
+    // the order of push.  What bounds it is one wave's stream: 8-D takes
+    // 8 + 36 + 8 (+ 36 with the gradient) of its instructions per four
+    // components instead of per one.  The next four components' parameters
+    // are read while these are worked on, where two sets fit.  The LDS copy
+    // is filled up to a multiple of four with components of the lowest
+    // finite log-weight and W = 0, whose weights are 0 and change no sum:
+    // straight-line passes instead of a branch per component left (a wave alone on its
+    // SIMD loses some 30 cycles a branch).
+    template <bool GRAD, int BMAX>
+    __device__ __forceinline__ static float eval_quad(QuadPtr P, int K, const float y[D], float g[D], bool want) {
         constexpr int B = LseBlock<STRIDE, GRAD, BMAX>::value;
+        constexpr bool AHEAD = D <= 8;
+        typedef float v4f __attribute__((ext_vector_type(4)));
+        typedef const __attribute__((address_space(3))) v4f *lds_v4ptr;
         float M = -INFINITY, S = 0.0f;
         float G[D];
 #pragma unroll
         for (int i = 0; i < D; ++i) G[i] = 0.0f;
-        int k = 0;
-        for (; k + B <= K; k += B) push<B, GRAD>(P, k, y, M, S, G, want);
-        for (; k < K; ++k) push<1, GRAD>(P, k, y, M, S, G, want);
+        v4f next[STRIDE / 4];
+        auto read = [&](int k0) {
+            const auto q = (lds_v4ptr)(P.L + (k0 + P.role) * STRIDE);
+#pragma unroll
+            for (int i = 0; i < STRIDE / 4; ++i) next[i] = q[i];
+        };
+        if (AHEAD) read(0);
+        for (int k0 = 0; k0 < K; k0 += 4) {
+            if (!AHEAD) read(k0);
+            float q[STRIDE];
+#pragma unroll
+            for (int i = 0; i < STRIDE; ++i) q[i] = next[i / 4][i % 4];
+            if (AHEAD) read(k0 + 4 < K ? k0 + 4 : k0);
+            float t = -q[0], v[D], u[D], dx[D];
+#pragma unroll
+            for (int i = 0; i < D; ++i) dx[i] = y[i] - q[1 + i];
+            const float *W = q + 1 + D;
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                float acc = W[i * (i + 1) / 2] * dx[0];
+#pragma unroll
+                for (int j = 1; j <= i; ++j) acc = fmaf(W[i * (i + 1) / 2 + j], dx[j], acc);
+                v[i] = acc;
+                t = fmaf(acc, acc, t);
+            }
+            if (GRAD && want) {
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    u[j] = 0.0f;
+#pragma unroll
+                    for (int i = j; i < D; ++i) u[j] = fmaf(W[i * (i + 1) / 2 + j], v[i], u[j]);
+                }
+            }
+            const float a = -t;
+            // lanes R .. R + N - 1 as one log-sum-exp block
+            auto block = [&](auto R, auto N) {
+                float ab[N], w[N], sc;
+                static_for<0, N>([&](auto b) { ab[b] = quad_bcast<R + b>(a); });
+                lse2_block<N, true>(M, S, ab, sc, w);
+                if (GRAD && want) {
+#pragma unroll
+                    for (int j = 0; j < D; ++j) G[j] *= sc;
+                    static_for<0, N>([&](auto b) {
+#pragma unroll
+                        for (int j = 0; j < D; ++j) G[j] = fmaf(w[b], quad_bcast<R + b>(u[j]), G[j]);
+                    });
+                }
+            };
+            // (the components past a multiple of B go one by one, which for
+            // B <= 2 is what a block with a filler gives)
+            constexpr std::integral_constant<int, 1> ONE{};
+            if (B <= 2 || k0 + 4 <= K)
+                static_for<0, 4 / B>([&](auto i) {
+                    block(std::integral_constant<int, i * B>{}, std::integral_constant<int, B>{});
+                });
+            else
+                static_for<0, 3>([&](auto i) { block(std::integral_constant<int, i>{}, ONE); });
+        }
         if (GRAD && want) {
             const float f = (-2.0f * LN2) / S;
 #pragma unroll
             for (int i = 0; i < D; ++i) g[i] = G[i] * f;
         }
         return lse2_ln(M, S);
+    }
+
+    template <bool GRAD, int BMAX = 4, class PT>
+    __device__ __forceinline__ static float eval(PT P, int K, const float y[D], float g[D], bool want) {
+        if constexpr (std::is_same<PT, QuadPtr>::value) {
+            return eval_quad<GRAD, BMAX>(P, K, y, g, want);
+        } else {
+            constexpr int B = LseBlock<STRIDE, GRAD, BMAX>::value;
+            float M = -INFINITY, S = 0.0f;
+            float G[D];
+#pragma unroll
+            for (int i = 0; i < D; ++i) G[i] = 0.0f;
+            int k = 0;
+            for (; k + B <= K; k += B) push<B, GRAD>(P, k, y, M, S, G, want);
+            for (; k < K; ++k) push<1, GRAD>(P, k, y, M, S, G, want);
+            if (GRAD && want) {
+                const float f = (-2.0f * LN2) / S;
+#pragma unroll
+                for (int i = 0; i < D; ++i) g[i] = G[i] * f;
+            }
+            return lse2_ln(M, S);
+        }
     }
 };
 
@@ -428,7 +601,11 @@ struct TargetOf<D, TGT_PSS> { using type = Pss<D>; };
 // lane wants it).
 template <int D, int TGT, bool GRAD, int BMAX = 4, class PT>
 __device__ __forceinline__ float log_target(PT P, int K, const float y[D], float g[D], bool want = true) {
-    const float lp = TargetOf<D, TGT>::type::template eval<GRAD, BMAX>(P, K, y, g, want);
+    float lp;
+    if constexpr (std::is_same<PT, RowPtr>::value)
+        lp = TargetOf<D, TGT>::type::template eval<GRAD, BMAX>(P.P, K, y, g, want);
+    else
+        lp = TargetOf<D, TGT>::type::template eval<GRAD, BMAX>(P, K, y, g, want);
     const bool in = in_unit_box<D>(y);
     if (GRAD && want) {
 #pragma unroll

@@ -112,8 +112,10 @@ __device__ __forceinline__ float log_u_state(const StepArgs &a, PT P, const floa
     if constexpr (LOC == LOC_RWU && TGT == TGT_ISO) {
         if (lp == -INFINITY) return 0.0f;
         float lq;
-        if constexpr (std::is_same<typename std::remove_cv<PT>::type, RowPtr>::value)
+        if constexpr (IsRow<typename std::remove_cv<PT>::type>::value)
             lq = GmmIsoInflow<D>::log_inflow_row(P, a.n_comp, y) - a.log_c;
+        else if constexpr (IsHeld<typename std::remove_cv<PT>::type>::value)
+            lq = GmmIsoInflow<D>::log_inflow(P.P, a.n_comp, y) - a.log_c;
         else
             lq = GmmIsoInflow<D>::log_inflow(P, a.n_comp, y) - a.log_c;
         const float M = fmaxf(lu, lq);
@@ -340,6 +342,9 @@ __device__ __forceinline__ void step_once(const StepArgs &a, PT P, uint32_t s,
                                           const StepRand<D> *pr = nullptr, RT mu_r = RT()) {
     static_assert(!PRE || (MU == MU_UNIFORM && !MH && !TILED), "precomputed inputs: uniform mu, restore only");
     constexpr int NB = NBlocks<D>::value;
+    // random-walk kinds with precomputed inputs run branch-free (selects):
+    // the same arithmetic, fewer exec-mask switches on the serial step path
+    constexpr bool FLAT = PRE && !uses_grad(LOC) && LOC != LOC_HMC;
     if constexpr (std::is_same<PT, const_fptr>::value) {
         // keep the scalar parameter loads inside the step: hoisted out of the
         // step loop, a large slab overflows the SGPRs and spills to VGPR lanes
@@ -371,7 +376,8 @@ __device__ __forceinline__ void step_once(const StepArgs &a, PT P, uint32_t s,
     float t2 = INFINITY;
     float inv_k = INFINITY;
     kill = false;
-    if (!MH && !no_kill) {
+    // (chains with precomputed inputs are never without killing)
+    if (!MH && (PRE || !no_kill)) {
         // t2 = E2 / k = E2 exp(log p - log u - ln c_tilde); p = 0 gives t2 = 0
         // (hardware 2^x: |x| 2^-24 relative, far inside the decision margins)
         inv_k = exp_rel(ch.lp - ch.lu - a.log_c);
@@ -381,7 +387,7 @@ __device__ __forceinline__ void step_once(const StepArgs &a, PT P, uint32_t s,
     // the holding time dt = min(t1, t2) ~ Exp(1 + k) whichever clock fires;
     // with rb_dt its conditional mean 1 / (1 + k) is accumulated instead
     float dt = kill ? t2 : t1;
-    if (rb_dt) dt = inv_k > 1e30f ? 1.0f : inv_k / (1.0f + inv_k);
+    if (__builtin_expect(rb_dt != 0, 0)) dt = inv_k > 1e30f ? 1.0f : inv_k / (1.0f + inv_k);
 
     bool large = false;
     if constexpr (MH) {
@@ -397,7 +403,8 @@ __device__ __forceinline__ void step_once(const StepArgs &a, PT P, uint32_t s,
     } else {
         // accumulate dt f(x_{i-1}) into the tour in flight
         ch.t_cur += dt;
-        if (f_p) ch.a_cur = fmaf(dt, exp_rel(ch.lp), ch.a_cur);
+        if (FLAT) ch.a_cur = f_p ? fmaf(dt, exp_rel(ch.lp), ch.a_cur) : ch.a_cur;
+        else if (f_p) ch.a_cur = fmaf(dt, exp_rel(ch.lp), ch.a_cur);
     }
     if (TGT == TGT_PSS && a.image) {
         // f = 1_pixel(x0, x1) at the pre-transition state (p = 0 off the box)
@@ -430,9 +437,6 @@ __device__ __forceinline__ void step_once(const StepArgs &a, PT P, uint32_t s,
         else ch.splat_acc += dt;
     }
     ch.last_dt = dt;
-    // random-walk kinds with precomputed inputs run branch-free (selects):
-    // the same arithmetic, fewer exec-mask switches on the serial step path
-    constexpr bool FLAT = PRE && !uses_grad(LOC) && LOC != LOC_HMC;
     if constexpr (FLAT) {
         ch.a_done += kill ? (double)ch.a_cur : 0.0;
         ch.t_done += kill ? (double)ch.t_cur : 0.0;

@@ -708,8 +708,9 @@ restore_status restore_init(restore_ctx **out, const restore_target *target, con
     c->mu = *mu;
     c->splat = sp;
     c->rand = ks.step_pre ? rp : RandPlan{};
-    // lanes a chain while that leaves at most two waves a SIMD
-    if (ks.step_lanes && cfg->n_chains * ks.lanes <= 2048LL * 64) c->lanes = ks.lanes;
+    // several lanes a chain while every SIMD can hold its waves at once
+    if (ks.step_lanes && cfg->n_chains * ks.lanes <= 1024LL * 64 * lane_waves(v.tgt, v.d, ks.lanes))
+        c->lanes = ks.lanes;
     fill_args(c);
 
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -75,6 +75,11 @@ __host__ __device__ constexpr int mu_slab_floats(int d, int K) { return 4 + K * 
 // full-covariance mixtures; the unadjusted jump process.
 constexpr int FULL_LANES = 4;
 constexpr int INFLOW_LANES = 16;
+// Waves a SIMD holds of them: from d = 13 a lane's component and state need
+// the registers of two.
+__host__ __device__ constexpr int lane_waves(int tgt, int d, int lanes) {
+    return lanes > 1 && !(tgt == TGT_FULL && d > 12) ? 2 : 1;
+}
 // Floats of a full-covariance slab in LDS with four lanes a chain: whole
 // passes of four components.
 __host__ __device__ constexpr int quad_slab_floats(int d, int K) { return (K + 3) / 4 * 4 * comp_stride(TGT_FULL, d); }

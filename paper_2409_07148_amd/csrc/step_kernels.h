@@ -151,7 +151,10 @@ struct PreFetch {
 // workgroup calls it.
 template <int D, int TGT, int G>
 __device__ __forceinline__ auto lane_target(const StepArgs &a, float *smem) {
-    if constexpr (G == 1) {
+    if constexpr (G == 1 && TGT == TGT_ISO) {
+        (void)smem;
+        return HeldPtr<D>((const_fptr)a.params, a.n_comp);
+    } else if constexpr (G == 1) {
         (void)smem;
         return (const_fptr)a.params;
     } else if constexpr (TGT == TGT_FULL) {
@@ -164,7 +167,7 @@ __device__ __forceinline__ auto lane_target(const StepArgs &a, float *smem) {
         return QuadPtr{(lds_fptr)smem, (int)(threadIdx.x % G)};
     } else {
         static_assert(G == INFLOW_LANES, "sixteen lanes a chain");
-        return RowPtr((const_fptr)a.params, D, a.n_comp, (int)(threadIdx.x % G));
+        return RowPtr<D>((const_fptr)a.params, a.n_comp, (int)(threadIdx.x % G));
     }
 }
 
@@ -174,7 +177,7 @@ __device__ __forceinline__ auto lane_target(const StepArgs &a, float *smem) {
 // one is loaded while the other's steps run.  The same chains as
 // step_kernel, bit for bit.
 template <int D, int TGT, int LOC, int G>
-__global__ __launch_bounds__(256, G > 1 ? 2 : 1) void step_pre_kernel(StepArgs a, const float *pre, int chunk, PreGen g) {
+__global__ __launch_bounds__(256, (lane_waves(TGT, D, G))) void step_pre_kernel(StepArgs a, const float *pre, int chunk, PreGen g) {
     if ((int64_t)blockIdx.x >= g.step_blocks) {
         pregen_block<D>(a, g, chunk);
         return;
@@ -191,26 +194,37 @@ __global__ __launch_bounds__(256, G > 1 ? 2 : 1) void step_pre_kernel(StepArgs a
     // the buffer base is wave-uniform and every byte offset fits in 32 bits
     // (at most 32 MiB per half), so the loads take the scalar-base mode
     const PFT pf(pre, a.n_chains, chunk, c, a.n_steps - 1);
-    unsigned long long n_acc = 0, n_kill = 0;
+    uint32_t n_acc = 0, n_kill = 0;   // a launch runs one chunk of steps
     bool kill = false, accept = false;
-    auto run = [&](const StepRand<D> (&r)[PF], int it0) {
-#pragma unroll
-        for (int j = 0; j < PF; ++j) {
-            if (it0 + j < a.n_steps) {
-                step_once<D, TGT, LOC, MU_UNIFORM, false, PT, false, false, false, true>(
-                    a, P, a.s0 + (uint32_t)(it0 + j), (uint32_t)c, ch, kill, accept, &r[j]);
-                n_acc += __popcll(__ballot(accept));
-                n_kill += __popcll(__ballot(kill));
-            }
-        }
+    auto step = [&](const StepRand<D> &r, int it) __attribute__((always_inline)) {
+        step_once<D, TGT, LOC, MU_UNIFORM, false, PT, false, false, false, true>(a, P, a.s0 + (uint32_t)it, (uint32_t)c,
+                                                                                ch, kill, accept, &r);
+        n_acc += (uint32_t)__popcll(__ballot(accept));
+        n_kill += (uint32_t)__popcll(__ballot(kill));
     };
     StepRand<D> A[PF], B[PF];
     pf.load(A, 0);
-    for (int it0 = 0; it0 < a.n_steps; it0 += 2 * PF) {
+    auto pair = [&](int it0, auto test) __attribute__((always_inline)) {
         pf.load(B, it0 + PF);
-        run(A, it0);
+#pragma unroll
+        for (int j = 0; j < PF; ++j)
+            if (!test || it0 + j < a.n_steps) step(A[j], it0 + j);
         pf.load(A, it0 + 2 * PF);
-        run(B, it0 + PF);
+#pragma unroll
+        for (int j = 0; j < PF; ++j)
+            if (!test || it0 + PF + j < a.n_steps) step(B[j], it0 + PF + j);
+    };
+    // the short steps of the isotropic mixtures: whole pairs of buffers
+    // without a test (a branch) per step, then the rest
+    int it0 = 0;
+    if constexpr (TGT == TGT_ISO) {
+        for (; it0 + 2 * PF <= a.n_steps; it0 += 2 * PF) pair(it0, std::false_type{});
+        for (; it0 < a.n_steps; ++it0) {
+            pf.fetch(A[0], it0);
+            step(A[0], it0);
+        }
+    } else {
+        for (; it0 < a.n_steps; it0 += 2 * PF) pair(it0, std::true_type{});
     }
     ch.status = (ch.status & ~(ST_LAST_KILL | ST_LAST_ACCEPT)) | (kill ? ST_LAST_KILL : 0u) |
                 (accept ? ST_LAST_ACCEPT : 0u);
@@ -224,7 +238,7 @@ __global__ __launch_bounds__(256, G > 1 ? 2 : 1) void step_pre_kernel(StepArgs a
 // them inline.  A wave ends when its last lane's tour is killed; survivors
 // of all a.n_steps steps are censored.  The same chains as drain_kernel.
 template <int D, int TGT, int LOC, int G>
-__global__ __launch_bounds__(256, G > 1 ? 2 : 1) void drain_pre_kernel(StepArgs a, const float *pre, int chunk, int n_pre) {
+__global__ __launch_bounds__(256, (lane_waves(TGT, D, G))) void drain_pre_kernel(StepArgs a, const float *pre, int chunk, int n_pre) {
     using PFT = PreFetch<D>;
     constexpr int PF = PFT::PF;
     extern __shared__ __attribute__((aligned(16))) float smem[];

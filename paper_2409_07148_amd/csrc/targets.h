@@ -33,6 +33,31 @@ struct MixPtr {
     lds_fptr L;
 };
 
+// An isotropic slab whose first four components stay in vector registers
+// through the step loop, for populations with a wave or less a SIMD: read at
+// each step they would put a scalar load's latency (some 200 cycles) on its
+// path.  A mixture of fewer is filled up with copies of its last one, which
+// nothing reads.
+constexpr int HELD = 4;
+template <int D>
+struct HeldPtr {
+    static constexpr int STRIDE = comp_stride(TGT_ISO, D);
+    const_fptr P;
+    float q[HELD * STRIDE];
+    __device__ __forceinline__ HeldPtr(const_fptr slab, int K) : P(slab) {
+        int zero;   // in a vector register, and the loads with it
+        asm("v_mov_b32_e32 %0, 0" : "=v"(zero));
+#pragma unroll
+        for (int k = 0; k < HELD; ++k)
+#pragma unroll
+            for (int i = 0; i < D + 2; ++i) q[k * STRIDE + i] = P[min(k, K - 1) * STRIDE + i + zero];
+    }
+};
+template <class PT>
+struct IsHeld : std::false_type {};
+template <int D>
+struct IsHeld<HeldPtr<D>> : std::true_type {};
+
 // Chains spread over several lanes (small populations and the tails of
 // drains, where a SIMD has a wave or two and a step costs its instruction
 // stream): every lane of a group of G holds the whole chain and computes
@@ -45,20 +70,25 @@ struct QuadPtr {
 };
 // The isotropic mixture of the unadjusted jump process, sixteen lanes a
 // chain (see GmmIsoInflow):
+template <int D>
 struct RowPtr {
-    const_fptr P;
+    HeldPtr<D> H;
     int role;   // the lane within its chain's sixteen
     // the first pass's component of this lane: means and inflow parameters
     float m[2], c, ivar, alpha, beta;
-    __device__ __forceinline__ RowPtr(const_fptr slab, int d, int K, int lane) : P(slab), role(lane) { load(d, K, 0); }
-    __device__ __forceinline__ void load(int d, int K, int k0) {
-        const int S = comp_stride(TGT_ISO, d), k = min(k0 + role / (2 * d), K - 1);
-        m[0] = P[k * S + 1];
-        m[1] = d == 2 ? P[k * S + 2] : 0.0f;
-        const const_fptr q = P + K * S + k * INFLOW_STRIDE;
+    __device__ __forceinline__ RowPtr(const_fptr slab, int K, int lane) : H(slab, K), role(lane) { load(K, 0); }
+    __device__ __forceinline__ void load(int K, int k0) {
+        const int S = comp_stride(TGT_ISO, D), k = min(k0 + role / (2 * D), K - 1);
+        m[0] = H.P[k * S + 1];
+        m[1] = D == 2 ? H.P[k * S + 2] : 0.0f;
+        const const_fptr q = H.P + K * S + k * INFLOW_STRIDE;
         c = q[0]; ivar = q[1]; alpha = q[2]; beta = q[3];
     }
 };
+template <class PT>
+struct IsRow : std::false_type {};
+template <int D>
+struct IsRow<RowPtr<D>> : std::true_type {};
 // lane R's x of each group of four, and of each row of sixteen
 template <int R>
 __device__ __forceinline__ float quad_bcast(float x) {
@@ -100,6 +130,7 @@ template <int D>
 struct GmmIso {
     static constexpr int STRIDE = comp_stride(TGT_ISO, D);
 
+    // P: the slab, or a pointer to the held components
     template <int B, bool GRAD, class PT>
     __device__ __forceinline__ static void push(PT P, int k0, const float y[D], float &M, float &S, float G[D],
                                                 bool want) {
@@ -137,8 +168,24 @@ struct GmmIso {
 #pragma unroll
         for (int i = 0; i < D; ++i) G[i] = 0.0f;
         int k = 0;
-        for (; k + B <= K; k += B) push<B, GRAD>(P, k, y, M, S, G, want);
-        for (; k < K; ++k) push<1, GRAD>(P, k, y, M, S, G, want);
+        if constexpr (IsHeld<PT>::value) {
+            const float *q = P.q;
+            if (K >= HELD) {
+#pragma unroll
+                for (int h = 0; h < HELD; h += B) push<B, GRAD>(q, h, y, M, S, G, want);
+                for (k = HELD; k + B <= K; k += B) push<B, GRAD>(P.P, k, y, M, S, G, want);
+                for (; k < K; ++k) push<1, GRAD>(P.P, k, y, M, S, G, want);
+            } else {
+                // (blocks first, as below; B is 1, 2 or 4)
+                if (B == 2 && K >= 2) push<B == 2 ? 2 : 1, GRAD>(q, 0, y, M, S, G, want);
+                else push<1, GRAD>(q, 0, y, M, S, G, want);
+                if (B != 2 && K >= 2) push<1, GRAD>(q, 1, y, M, S, G, want);
+                if (K == 3) push<1, GRAD>(q, 2, y, M, S, G, want);
+            }
+        } else {
+            for (; k + B <= K; k += B) push<B, GRAD>(P, k, y, M, S, G, want);
+            for (; k < K; ++k) push<1, GRAD>(P, k, y, M, S, G, want);
+        }
         if (GRAD && want) {
             const float f = (-2.0f * LN2) / S;
 #pragma unroll
@@ -164,14 +211,14 @@ struct GmmIso {
 // in order.
 template <int D>
 struct GmmIsoInflow {
-    __device__ __forceinline__ static float log_inflow_row(RowPtr P, int K, const float y[D]) {
+    __device__ __forceinline__ static float log_inflow_row(RowPtr<D> P, int K, const float y[D]) {
         static_assert(D <= 2, "one or two coordinates");
         constexpr int PER = 8 / D;   // components per pass
         const int i = D == 2 ? (P.role >> 1) & 1 : 0;
         const bool lower = (P.role & 1) != 0;
         float M = -INFINITY, S = 0.0f;
         for (int k0 = 0; k0 < K; k0 += PER) {
-            if (k0 > 0) P.load(D, K, k0);
+            if (k0 > 0) P.load(K, k0);
             float q = 0.0f, c = 0.0f;
 #pragma unroll
             for (int j = 0; j < D; ++j) {
@@ -602,8 +649,8 @@ struct TargetOf<D, TGT_PSS> { using type = Pss<D>; };
 template <int D, int TGT, bool GRAD, int BMAX = 4, class PT>
 __device__ __forceinline__ float log_target(PT P, int K, const float y[D], float g[D], bool want = true) {
     float lp;
-    if constexpr (std::is_same<PT, RowPtr>::value)
-        lp = TargetOf<D, TGT>::type::template eval<GRAD, BMAX>(P.P, K, y, g, want);
+    if constexpr (IsRow<PT>::value)
+        lp = TargetOf<D, TGT>::type::template eval<GRAD, BMAX>(P.H, K, y, g, want);
     else
         lp = TargetOf<D, TGT>::type::template eval<GRAD, BMAX>(P, K, y, g, want);
     const bool in = in_unit_box<D>(y);

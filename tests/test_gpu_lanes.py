@@ -81,3 +81,18 @@ def test_drain_of_a_large_population(R, d, K, local, chains):
         assert np.array_equal(whole[key], np.concatenate([p[0][key] for p in parts], axis=-1)), key
     for key in est:
         assert est[key] == sum(p[1][key] for p in parts), key
+
+
+@pytest.mark.parametrize("d,K,local", [(1, 1, "rwmh"), (2, 2, "mala"), (2, 3, "rwmh"), (2, 4, "rwmh"), (3, 5, "mala"),
+                                       (4, 3, "hmc"), (6, 9, "rwmh"), (16, 6, "mala")])
+def test_small_population_isotropic(R, d, K, local):
+    # the first four components held in registers, a chunk's steps in pairs
+    # of buffers and the odd ones after them
+    from workloads import gmm_iso_2d
+    rng = np.random.default_rng(11 * K + d)
+    params = {"weights": rng.dirichlet(np.full(K, 4.0)), "means": rng.uniform(0.2, 0.8, size=(K, d)),
+              "sigmas": np.full(K, 0.1)}
+    wl = gmm_iso_2d(1003, 23).with_(d=d, K=K, params=params, local=local, step=0.02, drain_cap=40, c_tilde=0.05,
+                                    n_leapfrog=2 if local == "hmc" else 0)
+    ref = _run(R, R.problem_from_workload(wl, flags=R.FLAG_INLINE_RNG), (23,))
+    _same(_run(R, R.problem_from_workload(wl), (1, 15, 7)), ref)

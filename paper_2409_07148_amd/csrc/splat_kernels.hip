@@ -11,6 +11,27 @@
 
 namespace restore {
 
+// *p += v in LDS, where addresses seldom meet.  The LDS float addition
+// retires one lane in about three cycles (67 M records at random pixels of
+// 64 KiB tiles: 338 us, with or without their loads), integer operations
+// several lanes a cycle, so a compare-and-swap on the bits is faster (106
+// us) though it also reads.  A lane that loses a few times, as on a pixel
+// that many records share, takes the float addition.
+__device__ __forceinline__ void lds_add_sparse(float *p, float v) {
+    uint32_t *w = reinterpret_cast<uint32_t *>(p);
+    uint32_t old = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int tries = 0; tries < 4; ++tries) {
+        const uint32_t seen = atomicCAS(w, old, __float_as_uint(__uint_as_float(old) + v));
+        if (seen == old) return;
+        old = seen;
+    }
+    atomicAdd(p, v);
+}
+
+// Fewest pixels of a band for which that pays: a workgroup adds 1024 records
+// at a time.
+constexpr int64_t SPARSE_PIXELS = 4096;
+
 // Per band b and slice: the slice's share of band b's records summed into a
 // 2^SPLAT_BAND_SHIFT-pixel LDS tile, written to partial[slice][band pixels].
 __global__ __launch_bounds__(1024) void splat_accumulate_kernel(SplatArgs s) {
@@ -30,6 +51,11 @@ __global__ __launch_bounds__(1024) void splat_accumulate_kernel(SplatArgs s) {
     // eight records in flight per thread, then their LDS additions
     const uint32_t nt = blockDim.x;
     uint32_t i = lo + t;
+    const bool sparse = s.n_pix - (int64_t)off >= SPARSE_PIXELS;
+    auto add = [&](uint32_t q, float v) {
+        if (sparse) lds_add_sparse(&tile[q - off], v);
+        else atomicAdd(&tile[q - off], v);
+    };
     for (; i + 7 * nt < hi; i += 8 * nt) {
         uint32_t q[8];
         float v[8];
@@ -39,9 +65,9 @@ __global__ __launch_bounds__(1024) void splat_accumulate_kernel(SplatArgs s) {
             v[k] = val[i + k * nt];
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) atomicAdd(&tile[q[k] - off], v[k]);
+        for (int k = 0; k < 8; ++k) add(q[k], v[k]);
     }
-    for (; i < hi; i += nt) atomicAdd(&tile[pix[i] - off], val[i]);
+    for (; i < hi; i += nt) add(pix[i], val[i]);
     __syncthreads();
     float *out = s.partial + (size_t)sl * ((size_t)s.n_bins << SPLAT_BAND_SHIFT) + off;
     for (int j = t; j < BAND; j += blockDim.x) out[j] = tile[j];
@@ -83,7 +109,22 @@ __global__ __launch_bounds__(IMG_THREADS) void image_batch_tours_kernel(ImageEst
     const int64_t C = (tile + 1 == T ? a.n_chains : ((tile + 1) * a.n_chains + T - 1) / T) - first;
     const int64_t lo = first + ((int64_t)b * C + B - 1) / B, hi = first + ((int64_t)(b + 1) * C + B - 1) / B;
     double v = 0.0;
-    for (int64_t c = lo + t; c < hi; c += IMG_THREADS)
+    // eight chains' loads in flight per thread (one at a time, a batch of
+    // 65 536 chains took 256 round trips to memory: 200 us, now 40)
+    int64_t c = lo + t;
+    for (; c + 7 * IMG_THREADS < hi; c += 8 * IMG_THREADS) {
+        double td[8], ad[8], n[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            td[k] = a.t_done[c + k * IMG_THREADS];
+            ad[k] = a.a_done[c + k * IMG_THREADS];
+            n[k] = (double)a.n_done[c + k * IMG_THREADS];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (isfinite(td[k]) && isfinite(ad[k])) v += n[k];
+    }
+    for (; c < hi; c += IMG_THREADS)
         if (isfinite(a.t_done[c]) && isfinite(a.a_done[c])) v += (double)a.n_done[c];
     sh[t] = v;
     __syncthreads();

@@ -242,8 +242,16 @@ __device__ __forceinline__ bool in_tile(const StepArgs &a, const float *y, int32
 // float32 (one fused multiply-add and a correctly rounded division each)
 __device__ __forceinline__ void tile_sample(const StepArgs &a, int32_t px0, int32_t py0, int32_t w, int32_t h,
                                             const float *cand, float *y) {
-    y[0] = __fdiv_rn(fmaf((float)w, cand[0], (float)px0), (float)a.image_w);
-    y[1] = __fdiv_rn(fmaf((float)h, cand[1], (float)py0), (float)a.image_h);
+    const float x0 = fmaf((float)w, cand[0], (float)px0), x1 = fmaf((float)h, cand[1], (float)py0);
+    // dividing by a power of two is multiplying by its reciprocal, exactly
+    // (one instruction against twelve; the same for every lane)
+    if (((a.image_w & (a.image_w - 1)) | (a.image_h & (a.image_h - 1))) == 0) {
+        y[0] = x0 * (1.0f / (float)a.image_w);
+        y[1] = x1 * (1.0f / (float)a.image_h);
+    } else {
+        y[0] = __fdiv_rn(x0, (float)a.image_w);
+        y[1] = __fdiv_rn(x1, (float)a.image_h);
+    }
 }
 
 template <int D, int LOC>

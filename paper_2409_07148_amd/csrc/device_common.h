@@ -78,6 +78,20 @@ __device__ __forceinline__ void draw_step(uint32_t step, uint32_t chain, uint32_
     }
 }
 
+// The correctly rounded square root of x >= 2^-96 (and +0), the value of
+// sqrtf: the hardware root s is within one ulp, and s - ulp / 2 and
+// s + ulp / 2 lie on the far side of the root when x - s pred(s) <= 0 and
+// x - s succ(s) > 0 (one rounding each).  Nine instructions, against the
+// library's sixteen, which also cover smaller numbers and infinities; every
+// float of [2^-96, 64] gives the same bits.
+__device__ __forceinline__ float sqrt_normal(float x) {
+    const float s = __builtin_amdgcn_sqrtf(x);
+    const float dn = __uint_as_float(__float_as_uint(s) - 1u), up = __uint_as_float(__float_as_uint(s) + 1u);
+    const float below = fmaf(-dn, s, x), above = fmaf(-up, s, x);
+    const float r = below <= 0.0f ? dn : s;
+    return above > 0.0f ? up : r;
+}
+
 // Box-Muller on consecutive candidate pairs: z_{2m} = rho cos(2 pi u_{2m+1}),
 // z_{2m+1} = rho sin(2 pi u_{2m+1}), rho = sqrt(-2 ln u_{2m}).  The hardware
 // sine/cosine take their argument in revolutions.  -2 ln u >= 1.1e-7 for
@@ -90,7 +104,7 @@ __device__ __forceinline__ void box_muller(const float cand[NC], float z[D]) {
 #pragma unroll
     for (int m = 0; 2 * m < D; ++m) {
         const float r2 = -2.0f * ln_u01(cand[2 * m]);
-        const float rho = HW_SQRT ? __builtin_amdgcn_sqrtf(r2) : sqrtf(r2);
+        const float rho = HW_SQRT ? __builtin_amdgcn_sqrtf(r2) : sqrt_normal(r2);
         const float ang = cand[2 * m + 1];
         z[2 * m] = rho * __builtin_amdgcn_cosf(ang);
         if (2 * m + 1 < D) z[2 * m + 1] = rho * __builtin_amdgcn_sinf(ang);

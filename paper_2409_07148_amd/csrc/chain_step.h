@@ -493,7 +493,7 @@ __device__ __forceinline__ void step_once(const StepArgs &a, PT P, uint32_t s,
 #pragma unroll
             for (int i = 0; i < D; ++i) z[i] = pr->z[i];
         } else {
-            box_muller<D, 4 * NB>(cand, z);
+            box_muller<D, 4 * NB, MH || TGT == TGT_PSS ? ROOT_NORMAL : ROOT_LIB>(cand, z);
         }
         if constexpr (LOC == LOC_HMC) {
             // leapfrog with unit mass from (x, rho_0 = z): half a momentum

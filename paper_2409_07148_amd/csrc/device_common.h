@@ -92,19 +92,25 @@ __device__ __forceinline__ float sqrt_normal(float x) {
     return above > 0.0f ? up : r;
 }
 
+// The square root of box_muller: the hardware's (about 1 ulp), or the
+// correctly rounded one by sqrt_normal or by the library (the same bits).
+enum Root : int { ROOT_HW, ROOT_NORMAL, ROOT_LIB };
+
 // Box-Muller on consecutive candidate pairs: z_{2m} = rho cos(2 pi u_{2m+1}),
 // z_{2m+1} = rho sin(2 pi u_{2m+1}), rho = sqrt(-2 ln u_{2m}).  The hardware
 // sine/cosine take their argument in revolutions.  -2 ln u >= 1.1e-7 for
-// the odd 23-bit uniforms, so HW_SQRT may take the hardware square root
-// without the library's denormal and rounding fix-ups (about 1 ulp): the
-// learned mu's sampler does; the local proposals keep sqrtf, with which the
-// uniform-mu step kernel schedules 1% faster.
-template <int D, int NC, bool HW_SQRT = false>
+// the odd 23-bit uniforms.  The learned mu's sampler takes the hardware
+// root; the image integrand's and the Metropolis-Hastings chain's moves
+// sqrt_normal (tile-stratified step 1.58 -> 1.53 ms per 64 steps, 8-D
+// Metropolis-Hastings 1% faster); the other moves keep sqrtf, with which the
+// 8-D restore kernel schedules better (a run of 12.6 against 13.0 ms).
+template <int D, int NC, Root ROOT = ROOT_LIB>
 __device__ __forceinline__ void box_muller(const float cand[NC], float z[D]) {
 #pragma unroll
     for (int m = 0; 2 * m < D; ++m) {
         const float r2 = -2.0f * ln_u01(cand[2 * m]);
-        const float rho = HW_SQRT ? __builtin_amdgcn_sqrtf(r2) : sqrt_normal(r2);
+        const float rho = ROOT == ROOT_HW ? __builtin_amdgcn_sqrtf(r2)
+                          : ROOT == ROOT_NORMAL ? sqrt_normal(r2) : sqrtf(r2);
         const float ang = cand[2 * m + 1];
         z[2 * m] = rho * __builtin_amdgcn_cosf(ang);
         if (2 * m + 1 < D) z[2 * m + 1] = rho * __builtin_amdgcn_sinf(ang);

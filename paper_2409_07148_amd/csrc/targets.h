@@ -627,7 +627,7 @@ struct MuGmm {
             for (int j = 1; j < K; ++j) pick += (cum[j] <= u_cat) ? 1 : 0;
         }
         float z[D];
-        box_muller<D, NC, true>(cand, z);
+        box_muller<D, NC, ROOT_HW>(cand, z);
         const float *ms = G + 4 + K * STRIDE + K + pick * 2 * D;
 #pragma unroll
         for (int i = 0; i < D; ++i) y[i] = fmaf(ms[D + i], z[i], ms[i]);

@@ -375,9 +375,9 @@ struct GmmFull {
     // components instead of per one.  The next four components' parameters
     // are read while these are worked on, where two sets fit.  The LDS copy
     // is filled up to a multiple of four with components of the lowest
-    // finite log-weight and W = 0, whose weights are 0 and change no sum:
-    // straight-line passes instead of a branch per component left (a wave alone on its
-    // SIMD loses some 30 cycles a branch).
+    // finite log-weight and W = 0, whose weights are 0 and change no sum.
+    // Whole passes are straight lines (a wave alone on its SIMD loses some
+    // 30 cycles a branch); the last one stops at the components left.
     template <bool GRAD, int BMAX>
     __device__ __forceinline__ static float eval_quad(QuadPtr P, int K, const float y[D], float g[D], bool want) {
         constexpr int B = LseBlock<STRIDE, GRAD, BMAX>::value;
@@ -395,12 +395,12 @@ struct GmmFull {
             for (int i = 0; i < STRIDE / 4; ++i) next[i] = q[i];
         };
         if (AHEAD) read(0);
-        for (int k0 = 0; k0 < K; k0 += 4) {
+        auto pass = [&](int k0, auto whole) __attribute__((always_inline)) {
             if (!AHEAD) read(k0);
             float q[STRIDE];
 #pragma unroll
             for (int i = 0; i < STRIDE; ++i) q[i] = next[i / 4][i % 4];
-            if (AHEAD) read(k0 + 4 < K ? k0 + 4 : k0);
+            if (AHEAD && whole) read(k0 + 4 < K ? k0 + 4 : k0);
             float t = -q[0], v[D], u[D], dx[D];
 #pragma unroll
             for (int i = 0; i < D; ++i) dx[i] = y[i] - q[1 + i];
@@ -423,7 +423,7 @@ struct GmmFull {
             }
             const float a = -t;
             // lanes R .. R + N - 1 as one log-sum-exp block
-            auto block = [&](auto R, auto N) {
+            auto block = [&](auto R, auto N) __attribute__((always_inline)) {
                 float ab[N], w[N], sc;
                 static_for<0, N>([&](auto b) { ab[b] = quad_bcast<R + b>(a); });
                 lse2_block<N, true>(M, S, ab, sc, w);
@@ -436,16 +436,26 @@ struct GmmFull {
                     });
                 }
             };
-            // (the components past a multiple of B go one by one, which for
-            // B <= 2 is what a block with a filler gives)
-            constexpr std::integral_constant<int, 1> ONE{};
-            if (B <= 2 || k0 + 4 <= K)
-                static_for<0, 4 / B>([&](auto i) {
+            if constexpr (whole) {
+                static_for<0, 4 / B>([&](auto i) __attribute__((always_inline)) {
                     block(std::integral_constant<int, i * B>{}, std::integral_constant<int, B>{});
                 });
-            else
-                static_for<0, 3>([&](auto i) { block(std::integral_constant<int, i>{}, ONE); });
-        }
+            } else {
+                // the components past a multiple of B go one by one; for B
+                // = 2 a filler in the block's second place gives the same
+                constexpr std::integral_constant<int, 1> ONE{};
+                if constexpr (B == 2) {
+                    block(std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
+                } else {
+                    block(std::integral_constant<int, 0>{}, ONE);
+                    if (K - k0 >= 2) block(ONE, ONE);
+                }
+                if (K - k0 == 3) block(std::integral_constant<int, 2>{}, ONE);
+            }
+        };
+        int k0 = 0;
+        for (; k0 + 4 <= K; k0 += 4) pass(k0, std::true_type{});
+        if (k0 < K) pass(k0, std::false_type{});
         if (GRAD && want) {
             const float f = (-2.0f * LN2) / S;
 #pragma unroll

@@ -84,14 +84,19 @@ struct ReduceArgs {
     double *partials;   // [n_blocks][RED_SLOTS]
     double *results;    // [RED_SLOTS]
     int32_t n_blocks;
+    // the run counters' copies, whose sums go to results[RED_COUNTERS + slot]
+    // as 64-bit integers, so that one copy brings everything to the host
+    const unsigned long long *counters;
 };
 
 enum ReduceSlot : int {
     RED_N = 0, RED_T, RED_A, RED_CENS, RED_CENS_T, RED_NONFINITE,
     RED_SS_T_N, RED_SS_A_N, RED_SS_A_T,
+    RED_COUNTERS,
     RED_SLOTS = 16
 };
 
+static_assert(RED_COUNTERS + CNT_LARGE_ACCEPTS < RED_SLOTS, "the counters fit behind the sums");
 hipError_t launch_reduce(const ReduceArgs &r, hipStream_t stream);
 
 // Per-tile float64 reduction of tile-stratified runs: for tile t (chains

@@ -57,6 +57,16 @@ __global__ __launch_bounds__(RED_THREADS) void reduce_final(ReduceArgs r, int fi
     for (int b = threadIdx.x; b < r.n_blocks; b += RED_THREADS)
         for (int s = 0; s < count; ++s) v[s] += r.partials[(size_t)b * RED_SLOTS + first + s];
     block_sum(sh, v, count, r.results + first);
+    if (first == RED_SS_T_N) {
+        // the counters: a wave per slot, a lane per copy
+        const int l = threadIdx.x % 64;
+        for (int slot = threadIdx.x / 64; slot <= CNT_LARGE_ACCEPTS; slot += RED_THREADS / 64) {
+            static_assert(CNT_SPREAD == 64, "a lane per copy");
+            unsigned long long n = r.counters[(size_t)l * CNT_LINE + slot];
+            for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+            if (l == 0) reinterpret_cast<unsigned long long *>(r.results)[RED_COUNTERS + slot] = n;
+        }
+    }
 }
 
 __global__ __launch_bounds__(RED_THREADS) void reduce_pass2(ReduceArgs r) {

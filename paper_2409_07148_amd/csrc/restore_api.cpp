@@ -618,6 +618,23 @@ __global__ void zero_u32_kernel(uint32_t *p, int n) {
     if (i < n) p[i] = 0u;
 }
 
+// The start of a run in one launch: a small slab out of the kernel's own
+// arguments, and the counters cleared (n_bins: the band counters, or 0).  The
+// copy from host memory and its synchronization, and a launch per array,
+// were a tenth of the time of the smallest runs.
+constexpr int SETUP_FLOATS = 768;
+struct SetupSlab {
+    float v[SETUP_FLOATS];
+};
+__global__ void setup_kernel(SetupSlab slab, int n, float *params, unsigned long long *counters, uint32_t *counts,
+                             uint32_t *bins, int n_bins) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) params[i] = slab.v[i];
+    if (i < CNT_SPREAD * CNT_LINE) counters[i] = 0ull;
+    if (i < 4) counts[i] = 0u;
+    if (i < n_bins) bins[i] = 0u;
+}
+
 __global__ void zero_u64_kernel(unsigned long long *p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0ull;
@@ -714,8 +731,14 @@ restore_status restore_init(restore_ctx **out, const restore_target *target, con
     fill_args(c);
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = hipMemcpyAsync(const_cast<float *>(c->args.params), slab.data(), slab.size() * sizeof(float),
-                                  hipMemcpyHostToDevice, s);
+    // (a stream in capture takes the copies, and is refused by them)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool small = slab.size() <= (size_t)SETUP_FLOATS && v.mu != MU_GMM &&
+                       hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    hipError_t e = hipSuccess;
+    if (!small)
+        e = hipMemcpyAsync(const_cast<float *>(c->args.params), slab.data(), slab.size() * sizeof(float),
+                           hipMemcpyHostToDevice, s);
     if (e != hipSuccess) { delete c; return hip_fail(e, "parameter upload"); }
     std::vector<float> mu_slab;
     if (v.mu == MU_GMM) {
@@ -733,14 +756,14 @@ restore_status restore_init(restore_ctx **out, const restore_target *target, con
         if (e != hipSuccess) { delete c; return hip_fail(e, "mu upload"); }
     }
     // the upload reads a host vector that goes away: finish it before returning
-    e = hipStreamSynchronize(s);
+    if (!small) e = hipStreamSynchronize(s);
     if (e != hipSuccess) { delete c; return hip_fail(e, "parameter upload"); }
-    hipLaunchKernelGGL(zero_u64_kernel, dim3(CNT_SPREAD * CNT_LINE / 256), dim3(256), 0, s, c->args.counters,
-                       CNT_SPREAD * CNT_LINE);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, at<uint32_t>(c, c->lay.counts), 4);
-    if (sp.n_bins)
-        hipLaunchKernelGGL(zero_u32_kernel, dim3(SPLAT_MAX_BANDS * SPLAT_COUNTER_STRIDE / 256), dim3(256), 0, s,
-                           c->args.bin_count, SPLAT_MAX_BANDS * SPLAT_COUNTER_STRIDE);
+    SetupSlab by_value{};
+    if (small) std::memcpy(by_value.v, slab.data(), slab.size() * sizeof(float));
+    const int n_bins = sp.n_bins ? SPLAT_MAX_BANDS * SPLAT_COUNTER_STRIDE : 0;
+    hipLaunchKernelGGL(setup_kernel, grid_for(std::max(CNT_SPREAD * CNT_LINE, n_bins), 256), dim3(256), 0, s, by_value,
+                       small ? (int)slab.size() : 0, const_cast<float *>(c->args.params), c->args.counters,
+                       at<uint32_t>(c, c->lay.counts), c->args.bin_count, n_bins);
     if (sp.fixed)
         hipLaunchKernelGGL(zero_u64_kernel, grid_for(sp.n_pix, 256), dim3(256), 0, s, c->args.image_fx,
                            (int)sp.n_pix);
@@ -1036,19 +1059,15 @@ restore_status restore_estimate(restore_ctx *c, restore_estimate_out *out, void 
     r.results = at<double>(c, c->lay.results);
     const int64_t want = (c->cfg.n_chains + 255) / 256;
     r.n_blocks = (int32_t)(want < RED_BLOCKS ? want : RED_BLOCKS);
+    r.counters = c->args.counters;
     hipError_t e = launch_reduce(r, s);
     if (e != hipSuccess) return hip_fail(e, "reduce launch");
     double res[RED_SLOTS];
-    std::vector<unsigned long long> lines((size_t)CNT_SPREAD * CNT_LINE);
     e = hipMemcpyAsync(res, r.results, sizeof(res), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(lines.data(), c->args.counters, lines.size() * sizeof(unsigned long long),
-                           hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "estimate readback");
     unsigned long long cnt[CNT_SLOTS] = {};
-    for (int l = 0; l < CNT_SPREAD; ++l)
-        for (int j = 0; j < CNT_SLOTS; ++j) cnt[j] += lines[(size_t)l * CNT_LINE + j];
+    std::memcpy(cnt, res + RED_COUNTERS, sizeof(unsigned long long) * (CNT_LARGE_ACCEPTS + 1));
 
     const double N = res[RED_N], T = res[RED_T], A = res[RED_A];
     const double n_ok = (double)c->cfg.n_chains - res[RED_NONFINITE];

@@ -190,27 +190,59 @@ __global__ __launch_bounds__(BR_THREADS) void batch_reduce_kernel(BatchArgs b) {
     const BatchTarget t = b.targets[blockIdx.x];
     const int64_t o = t.chain_offset;
     double v[6] = {0, 0, 0, 0, 0, 0};
-    for (int c = threadIdx.x; c < t.n_chains; c += BR_THREADS) {
-        const double td = b.t_done[o + c], ad = b.a_done[o + c];
-        if (!isfinite(td) || !isfinite(ad)) { v[5] += 1.0; continue; }
-        v[0] += (double)b.n_done[o + c];
+    auto sums = [&](double td, double ad, uint32_t n, uint32_t status, float t_cur) {
+        if (!isfinite(td) || !isfinite(ad)) { v[5] += 1.0; return; }
+        v[0] += (double)n;
         v[1] += td;
         v[2] += ad;
-        if (b.status[o + c] & ST_CENSORED) { v[3] += 1.0; v[4] += (double)b.t_cur[o + c]; }
+        if (status & ST_CENSORED) { v[3] += 1.0; v[4] += (double)t_cur; }
+    };
+    // eight chains' loads in flight per thread, added in their order: a
+    // target of 2^18 chains is 1024 round trips to memory a pass otherwise
+    const int stop = t.n_chains - 7 * BR_THREADS;
+    int c = threadIdx.x;
+    for (; c < stop; c += 8 * BR_THREADS) {
+        double td[8], ad[8];
+        uint32_t nd[8], st[8];
+        float tc[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t i = o + c + k * BR_THREADS;
+            td[k] = b.t_done[i];
+            ad[k] = b.a_done[i];
+            nd[k] = b.n_done[i];
+            st[k] = b.status[i];
+            tc[k] = b.t_cur[i];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sums(td[k], ad[k], nd[k], st[k], tc[k]);
     }
+    for (; c < t.n_chains; c += BR_THREADS)
+        sums(b.t_done[o + c], b.a_done[o + c], b.n_done[o + c], b.status[o + c], b.t_cur[o + c]);
     br_sum(sh, v, 6);
     const double N = v[0], T = v[1], A = v[2];
     const double R_tn = N > 0 ? T / N : 0.0, R_an = N > 0 ? A / N : 0.0, R_at = T > 0 ? A / T : 0.0;
     double r[3] = {0, 0, 0};
-    for (int c = threadIdx.x; c < t.n_chains; c += BR_THREADS) {
-        const double td = b.t_done[o + c], ad = b.a_done[o + c];
-        if (!isfinite(td) || !isfinite(ad)) continue;
-        const double n = (double)b.n_done[o + c];
+    auto squares = [&](double td, double ad, double n) {
+        if (!isfinite(td) || !isfinite(ad)) return;
         const double e1 = td - R_tn * n, e2 = ad - R_an * n, e3 = ad - R_at * td;
         r[0] += e1 * e1;
         r[1] += e2 * e2;
         r[2] += e3 * e3;
+    };
+    for (c = threadIdx.x; c < stop; c += 8 * BR_THREADS) {
+        double td[8], ad[8], nd[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t i = o + c + k * BR_THREADS;
+            td[k] = b.t_done[i];
+            ad[k] = b.a_done[i];
+            nd[k] = (double)b.n_done[i];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) squares(td[k], ad[k], nd[k]);
     }
+    for (; c < t.n_chains; c += BR_THREADS) squares(b.t_done[o + c], b.a_done[o + c], (double)b.n_done[o + c]);
     br_sum(sh, r, 3);
     if (threadIdx.x == 0) {
         double *out = b.results + (size_t)blockIdx.x * BS_SLOTS;

@@ -621,11 +621,14 @@ __global__ void zero_u32_kernel(uint32_t *p, int n) {
 // The start of a run in one launch: a small slab out of the kernel's own
 // arguments, and the counters cleared (n_bins: the band counters, or 0).  The
 // copy from host memory and its synchronization, and a launch per array,
-// were a tenth of the time of the smallest runs.
-constexpr int SETUP_FLOATS = 768;
+// were a tenth of the time of the smallest runs.  A kernel takes 4 KiB of
+// arguments; 256 bytes of them are left for the others, the compiler's own
+// among them.
+constexpr int SETUP_FLOATS = (4096 - 256) / sizeof(float);
 struct SetupSlab {
     float v[SETUP_FLOATS];
 };
+static_assert(SETUP_FLOATS <= CNT_SPREAD * CNT_LINE, "a thread per float");
 __global__ void setup_kernel(SetupSlab slab, int n, float *params, unsigned long long *counters, uint32_t *counts,
                              uint32_t *bins, int n_bins) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -760,14 +763,20 @@ restore_status restore_init(restore_ctx **out, const restore_target *target, con
     if (e != hipSuccess) { delete c; return hip_fail(e, "parameter upload"); }
     SetupSlab by_value{};
     if (small) std::memcpy(by_value.v, slab.data(), slab.size() * sizeof(float));
-    const int n_bins = sp.n_bins ? SPLAT_MAX_BANDS * SPLAT_COUNTER_STRIDE : 0;
-    hipLaunchKernelGGL(setup_kernel, grid_for(std::max(CNT_SPREAD * CNT_LINE, n_bins), 256), dim3(256), 0, s, by_value,
-                       small ? (int)slab.size() : 0, const_cast<float *>(c->args.params), c->args.counters,
-                       at<uint32_t>(c, c->lay.counts), c->args.bin_count, n_bins);
-    if (sp.fixed)
-        hipLaunchKernelGGL(zero_u64_kernel, grid_for(sp.n_pix, 256), dim3(256), 0, s, c->args.image_fx,
-                           (int)sp.n_pix);
     StepArgs a = c->args;
+    int n_slab = small ? (int)slab.size() : 0, n_bins = sp.n_bins ? SPLAT_MAX_BANDS * SPLAT_COUNTER_STRIDE : 0;
+    float *params = const_cast<float *>(a.params);
+    uint32_t *counts = at<uint32_t>(c, c->lay.counts);
+    void *sargs[] = {&by_value, &n_slab, &params, &a.counters, &counts, &a.bin_count, &n_bins};
+    e = hipLaunchKernel((const void *)setup_kernel, grid_for(std::max(CNT_SPREAD * CNT_LINE, n_bins), 256), dim3(256),
+                        sargs, 0, s);
+    if (e != hipSuccess) { delete c; return hip_fail(e, "setup launch"); }
+    if (sp.fixed) {
+        int n_pix = (int)sp.n_pix;
+        void *zargs[] = {&a.image_fx, &n_pix};
+        e = hipLaunchKernel((const void *)zero_u64_kernel, grid_for(sp.n_pix, 256), dim3(256), zargs, 0, s);
+        if (e != hipSuccess) { delete c; return hip_fail(e, "image clearing launch"); }
+    }
     void *kargs[] = {&a};
     e = hipLaunchKernel(ks.init, grid_for(cfg->n_chains, 256), dim3(256), kargs, 0, s);
     if (e != hipSuccess) { delete c; return hip_fail(e, "init launch"); }

@@ -162,7 +162,7 @@ __device__ __forceinline__ auto lane_target(const StepArgs &a, float *smem) {
         constexpr int S = comp_stride(TGT_FULL, D);
         const int n = a.n_comp * S, all = quad_slab_floats(D, a.n_comp);
         for (int i = threadIdx.x; i < all; i += blockDim.x)
-            smem[i] = i < n ? a.params[i] : i % S == 0 ? -0x1.fffffep127f : 0.0f;
+            smem[i] = i < n ? a.params[i] : i % S == 0 ? -INFINITY : 0.0f;
         __syncthreads();
         return QuadPtr{(lds_fptr)smem, (int)(threadIdx.x % G)};
     } else {

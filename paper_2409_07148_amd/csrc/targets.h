@@ -374,8 +374,9 @@ struct GmmFull {
     // 8 + 36 + 8 (+ 36 with the gradient) of its instructions per four
     // components instead of per one.  The next four components' parameters
     // are read while these are worked on, where two sets fit.  The LDS copy
-    // is filled up to a multiple of four with components of the lowest
-    // finite log-weight and W = 0, whose weights are 0 and change no sum.
+    // is filled up to a multiple of four with components of log-weight -inf
+    // and W = 0: beside a component of the mixture their weights are 0 and
+    // change no sum, nor the NaN of a density whose terms are all -inf.
     // Whole passes are straight lines (a wave alone on its SIMD loses some
     // 30 cycles a branch); the last one stops at the components left.
     template <bool GRAD, int BMAX>

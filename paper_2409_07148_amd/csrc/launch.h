@@ -20,6 +20,7 @@ struct KernelSet {
     const void *step_mh_split = nullptr;
     const void *drain = nullptr;
     const void *drain_lds = nullptr;
+    const void *drain_wide = nullptr;        // short lists, several lanes a chain
     const void *step_binned = nullptr;       // image integrand: binned splats
     const void *step_binned_lds = nullptr;
     const void *step_mh = nullptr;           // the MH reference chain M^l (c_tilde = 0)

@@ -116,9 +116,6 @@ SplatPlan splat_plan(const restore_config *cfg, int tgt) {
     return sp;
 }
 
-// Longest list that a drain runs with several lanes a chain: two waves a SIMD.
-constexpr int64_t DRAIN_WIDE_MAX = 2048LL * 64 / FULL_LANES;
-
 constexpr int64_t RAND_HALF_BYTES = 32LL << 20;
 
 RandPlan rand_plan(const restore_config *cfg, int tgt, int d, int mu) {
@@ -729,7 +726,7 @@ restore_status restore_init(restore_ctx **out, const restore_target *target, con
     c->splat = sp;
     c->rand = ks.step_pre ? rp : RandPlan{};
     // several lanes a chain while every SIMD can hold its waves at once
-    if (ks.step_lanes && cfg->n_chains * ks.lanes <= 1024LL * 64 * lane_waves(v.tgt, v.d, ks.lanes))
+    if (ks.step_lanes && cfg->n_chains * ks.lanes <= SIMD_THREADS * lane_waves(v.tgt, v.d, ks.lanes))
         c->lanes = ks.lanes;
     fill_args(c);
 
@@ -926,12 +923,7 @@ restore_status restore_drain(restore_ctx *c, void *stream) {
     hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, s, counts, 4);
     const bool tiled = c->splat.n_tiles > 0;
     const void *fn = tiled ? c->ks.drain_tiled : c->lds ? c->ks.drain_lds : c->ks.drain;
-    const bool wide = drains_wide(c->v.tgt, c->v.mu) && !c->lds;
-    const size_t shm = tiled ? 0
-                       : wide ? sizeof(float) * (size_t)quad_slab_floats(c->v.d, c->v.K)
-                              : kernel_lds_bytes(c, c->lds, false);
-    // (the grid has a lane for every chain)
-    const int wide_max = wide ? (int)std::min<int64_t>(DRAIN_WIDE_MAX, c->cfg.n_chains / FULL_LANES) : 0;
+    const size_t shm = tiled ? 0 : kernel_lds_bytes(c, c->lds, false);
     // chunks of 1, 2, 4, ... steps: survivors are compacted between chunks
     // while many chains retire, and the long tail takes few launches.  A
     // population below 2^16 chains has too few waves to fill the chip, so
@@ -941,23 +933,46 @@ restore_status restore_drain(restore_ctx *c, void *stream) {
     int32_t remaining = c->cfg.drain_cap;
     int64_t chunk = c->cfg.n_chains < (1LL << 16) ? std::max<int64_t>(1, c->cfg.drain_cap) : 1;
     uint32_t s0 = (uint32_t)c->steps_taken;
-    for (int j = 0;; ++j) {
+    // A list of at most a wave a SIMD goes on with four lanes a chain, in
+    // launches that end 63, 255, 1023, ... steps into the drain and with it
+    // (each costs a launch, some 3 us, where the list is empty or long).  Not
+    // for one or two components: half the lanes or more would work for
+    // nothing, and drains took 0.88 to 1.26 times as long.
+    const bool wide = c->ks.drain_wide && !c->lds && c->v.K >= 3 && remaining > chunk;
+    int wide_max = wide ? (int)(SIMD_THREADS / FULL_LANES) : 0;
+    uint32_t *wide_from = counts + 3;
+    uint32_t wide_done = s0;
+    int np = c->n_params;
+    StepArgs a = c->args;   // (no list: every chain)
+    int q = 0;              // launches so far: they take the lists and counters in turn
+    auto launch = [&](const void *k, int64_t threads, size_t lds, int last) {
+        uint32_t *list_out = lists[q % 2];
+        uint32_t *count_out = counts + ((q + 1) % 3);
+        uint32_t *count_zero = counts + ((q + 2) % 3);
+        void *one[] = {&a, &np, &list_out, &count_out, &count_zero, &last, &wide_max, &wide_from};
+        void *many[] = {&a, &wide_from, &wide_done, &s0, &list_out, &count_out, &count_zero, &last};
+        hipError_t e = hipLaunchKernel(k, grid_for(threads, c->block), dim3(c->block), k == fn ? one : many, lds, s);
+        a.list = list_out;
+        a.list_count = count_out;
+        ++q;
+        return e;
+    };
+    for (int64_t wide_end = 63;;) {
         const int32_t L = remaining < chunk ? remaining : (int32_t)chunk;
-        const int last = (remaining - L) == 0 ? 1 : 0;
-        StepArgs a = c->args;
-        a.list = j == 0 ? nullptr : lists[(j - 1) % 2];
-        a.list_count = j == 0 ? nullptr : counts + (j % 3);
+        remaining -= L;
+        const int last = remaining == 0 ? 1 : 0;
         a.s0 = s0;
         a.n_steps = L;
-        int np = c->n_params;
-        uint32_t *list_out = lists[j % 2];
-        uint32_t *count_out = counts + ((j + 1) % 3);
-        uint32_t *count_zero = counts + ((j + 2) % 3);
-        void *kargs[] = {&a, &np, &list_out, &count_out, &count_zero, (void *)&last, (void *)&wide_max};
-        hipError_t e = hipLaunchKernel(fn, grid_for(c->cfg.n_chains, c->block), dim3(c->block), kargs, shm, s);
+        hipError_t e = launch(fn, c->cfg.n_chains, shm, last);
         if (e != hipSuccess) return hip_fail(e, "drain launch");
         s0 += (uint32_t)L;
-        remaining -= L;
+        if (wide && (last || (c->cfg.drain_cap - remaining >= wide_end && remaining >= 2 * wide_end))) {
+            e = launch(c->ks.drain_wide, (int64_t)wide_max * FULL_LANES,
+                       sizeof(float) * (size_t)quad_slab_floats(c->v.d, c->v.K), last);
+            if (e != hipSuccess) return hip_fail(e, "drain launch");
+            wide_done = s0;
+            wide_end = 4 * wide_end + 3;
+        }
         if (last) break;
         chunk *= 2;
     }

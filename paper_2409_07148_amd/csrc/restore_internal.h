@@ -75,6 +75,8 @@ __host__ __device__ constexpr int mu_slab_floats(int d, int K) { return 4 + K * 
 // full-covariance mixtures; the unadjusted jump process.
 constexpr int FULL_LANES = 4;
 constexpr int INFLOW_LANES = 16;
+// One wave on each SIMD of the chip (256 CUs of four), in threads.
+constexpr int64_t SIMD_THREADS = 1024LL * 64;
 // Waves a SIMD holds of them: from d = 13 a lane's component and state need
 // the registers of two.
 __host__ __device__ constexpr int lane_waves(int tgt, int d, int lanes) {
@@ -83,8 +85,6 @@ __host__ __device__ constexpr int lane_waves(int tgt, int d, int lanes) {
 // Floats of a full-covariance slab in LDS with four lanes a chain: whole
 // passes of four components.
 __host__ __device__ constexpr int quad_slab_floats(int d, int K) { return (K + 3) / 4 * 4 * comp_stride(TGT_FULL, d); }
-// the drain kernels that take it for short lists
-__host__ __device__ constexpr bool drains_wide(int tgt, int mu) { return tgt == TGT_FULL && mu == MU_UNIFORM; }
 // Full-covariance components read half from LDS (MixRows), from this
 // dimension on (at d = 3 a component's five floats fill two 16-byte reads:
 // 69 610 chains ran 3.5% slower); the first row of

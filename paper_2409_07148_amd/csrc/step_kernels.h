@@ -462,14 +462,16 @@ __global__ __launch_bounds__(256) void step_tiled_kernel(StepArgs a, int n_param
     }
 }
 
-// Drain steps of the chain at place `at` of the input list of n_in chains
+// n_steps drain steps from step s0 of the chain at place `at` of the input
+// list of n_in chains
 // (a.list; all chains in order without one), G lanes a chain: until its tour
 // in flight is killed, without regeneration.  Survivors of this chunk are
 // compacted into the output list with one ballot and one atomic per wave;
 // on the last chunk they are marked censored instead.
 template <int D, int TGT, int LOC, int MU, bool TILED, int G, class PT, class RT>
-__device__ __forceinline__ void drain_chain(const StepArgs &a, PT P, RT MR, int64_t at, int64_t n_in,
-                                            uint32_t *list_out, uint32_t *count_out, int last_chunk) {
+__device__ __forceinline__ void drain_chain(const StepArgs &a, PT P, RT MR, uint32_t s0, int n_steps, int64_t at,
+                                            int64_t n_in, uint32_t *list_out, uint32_t *count_out,
+                                            int last_chunk) {
     const int64_t idx = at / G;
     if (idx >= n_in) return;
     const bool first = at % G == 0;
@@ -479,14 +481,14 @@ __device__ __forceinline__ void drain_chain(const StepArgs &a, PT P, RT MR, int6
     bool alive = (ch.status & ST_ALIVE) != 0u;
     unsigned long long n_t = 0, n_acc = 0, n_kill = 0;
     bool stepped = false, kill_last = false, acc_last = false;
-    for (int it = 0; it < a.n_steps; ++it) {
+    for (int it = 0; it < n_steps; ++it) {
         const unsigned long long live = __ballot(alive);
         if (live == 0ull) break;
         n_t += __popcll(live);
         bool kill = false, accept = false;
         if (alive) {
             step_once<D, TGT, LOC, MU, true, PT, false, false, TILED, false, RT>(
-                a, P, a.s0 + (uint32_t)it, c, ch, kill, accept, nullptr, MR);
+                a, P, s0 + (uint32_t)it, c, ch, kill, accept, nullptr, MR);
             stepped = true;
             kill_last = kill;
             acc_last = accept;
@@ -520,32 +522,64 @@ __device__ __forceinline__ void drain_chain(const StepArgs &a, PT P, RT MR, int6
     }
 }
 
-// Drain.  The grid covers every chain; once the list is short enough
-// (wide_max chains: a wave or two a SIMD) a full-covariance chain takes
-// FULL_LANES lanes, as what is left of the drain is the length of its
-// longest tours.
+// Drain, one lane a chain.  The grid covers every chain.  A list of at most
+// wide_max chains is left to drain_wide_kernel: it is passed on as it is, and
+// *wide_from holds the step at which that began.
 template <int D, int TGT, int LOC, int MU, bool LDS, bool TILED = false>
 __global__ __launch_bounds__(256) void drain_kernel(StepArgs a, int n_param_floats, uint32_t *list_out,
                                                      uint32_t *count_out, uint32_t *count_zero,
-                                                     int last_chunk, int wide_max) {
+                                                     int last_chunk, int wide_max, uint32_t *wide_from) {
     extern __shared__ __attribute__((aligned(16))) float smem[];
     if (blockIdx.x == 0 && threadIdx.x == 0) *count_zero = 0u;
     const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t n_in = a.list ? (int64_t)*a.list_count : a.n_chains;
-    if constexpr (drains_wide(TGT, MU) && !LDS) {
-        if (n_in <= wide_max) {
-            if ((int64_t)blockIdx.x * blockDim.x >= n_in * FULL_LANES) return;
-            const auto Q = lane_target<D, TGT, FULL_LANES>(a, smem);
-            drain_chain<D, TGT, LOC, MU, TILED, FULL_LANES>(a, Q, (const_fptr) nullptr, at, n_in, list_out, count_out,
-                                                            last_chunk);
-            return;
+    if (n_in <= wide_max) {
+        if (at < n_in) list_out[at] = a.list[at];
+        if (at == 0) {
+            *count_out = (uint32_t)n_in;
+            if (*wide_from == 0u) *wide_from = a.s0;
         }
+        return;
     }
     const auto P = stage_params<LDS>(a.params, n_param_floats, smem);
     // (tile-stratified runs have the uniform mu)
     const auto MR = stage_mu<D, TILED ? MU_UNIFORM : MU>(a, smem + mu_lds_offset(LDS, false, n_param_floats, D, a.n_comp));
-    drain_chain<D, TGT, LOC, MU, TILED, 1, decltype(P), decltype(MR)>(a, P, MR, at, n_in, list_out, count_out,
-                                                                      last_chunk);
+    drain_chain<D, TGT, LOC, MU, TILED, 1, decltype(P), decltype(MR)>(a, P, MR, a.s0, a.n_steps, at, n_in,
+                                                                      list_out, count_out, last_chunk);
+}
+
+// Drain of a list that has become short (*wide_from is not 0), from there or
+// from the last such launch's end (`done`) to step `end`: what is left is the
+// length of its longest tours, so a full-covariance chain takes FULL_LANES
+// lanes, and compaction between launches matters little.  It does matter
+// over hundreds of steps: waves whose steps have drifted apart slow each
+// other down (a 5-D Hamiltonian list of 3822 chains, 434 of them left after
+// 128 steps: 3.4 us a step until step 64, 8.4 from step 128 in one launch,
+// 3.7 in a compacted one).  A kernel of its own: in one with the
+// form above, that form had this one's registers and LDS, and half its waves
+// (8-D Langevin 147 -> 234 registers; drains whose lists stay long ran 5-30%
+// slower).  A list that is still long is passed on as it is.
+template <int D, int TGT, int LOC>
+__global__ __launch_bounds__(256) void drain_wide_kernel(StepArgs a, const uint32_t *wide_from, uint32_t done,
+                                                         uint32_t end, uint32_t *list_out, uint32_t *count_out,
+                                                         uint32_t *count_zero, int last) {
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *count_zero = 0u;
+    const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t n_in = (int64_t)*a.list_count;
+    // (in a scalar register, as a kernel argument would be)
+    const uint32_t from = (uint32_t)__builtin_amdgcn_readfirstlane((int)*wide_from);
+    if (from == 0u) {
+        if (last) return;
+        for (int64_t i = at; i < n_in; i += (int64_t)gridDim.x * blockDim.x) list_out[i] = a.list[i];
+        if (at == 0) *count_out = (uint32_t)n_in;
+        return;
+    }
+    if ((int64_t)blockIdx.x * blockDim.x >= n_in * FULL_LANES) return;
+    const uint32_t s0 = max(from, done);
+    const auto Q = lane_target<D, TGT, FULL_LANES>(a, smem);
+    drain_chain<D, TGT, LOC, MU_UNIFORM, false, FULL_LANES>(a, Q, (const_fptr) nullptr, s0, (int)(end - s0), at, n_in,
+                                                            list_out, count_out, last);
 }
 
 // x_0 ~ mu (purpose INIT, step 0), cached log p / log u / grad, zero sums.
@@ -617,6 +651,7 @@ static KernelSet make_set() {
     }
     k.drain = (const void *)drain_kernel<D, TGT, LOC, MU, false>;
     k.drain_lds = (const void *)drain_kernel<D, TGT, LOC, MU, true>;
+    if constexpr (TGT == TGT_FULL && MU == MU_UNIFORM) k.drain_wide = (const void *)drain_wide_kernel<D, TGT, LOC>;
     if constexpr (TGT != TGT_PSS && MU == MU_UNIFORM) {
         k.rand_prepass = (const void *)rand_prepass_kernel<D>;
         k.step_pre = (const void *)step_pre_kernel<D, TGT, LOC, 1>;

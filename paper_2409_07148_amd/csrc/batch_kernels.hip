@@ -130,7 +130,7 @@ __device__ __forceinline__ void run_item_dispatch(const BatchArgs &b, const Batc
 // Persistent: every workgroup pops items until the queue is empty, so every
 // wave reaches the exit once all items are taken.
 template <int DLO, int DHI, int MU, bool SPLIT>
-__global__ __launch_bounds__(256, (min_waves(SPLIT, DHI))) void batch_persistent_kernel(BatchArgs b) {
+__global__ __launch_bounds__(256, (min_waves(SPLIT, LOC_RWMH, DHI))) void batch_persistent_kernel(BatchArgs b) {
     __shared__ int32_t item_sh;
     __shared__ float mu_sh[MU == MU_GMM ? MU_LDS_FLOATS : 1];
     for (;;) {
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256, (min_waves(SPLIT, DHI))) void batch_persistent
 
 // One launch per target (the comparison mode): block i takes the i-th tile.
 template <int DLO, int DHI, int MU, bool SPLIT>
-__global__ __launch_bounds__(256, (min_waves(SPLIT, DHI))) void batch_target_kernel(BatchArgs b, int32_t target) {
+__global__ __launch_bounds__(256, (min_waves(SPLIT, LOC_RWMH, DHI))) void batch_target_kernel(BatchArgs b, int32_t target) {
     __shared__ float mu_sh[MU == MU_GMM ? MU_LDS_FLOATS : 1];
     const BatchTarget t = b.targets[target];
     WorkItem w;

@@ -106,11 +106,18 @@ __host__ __device__ constexpr int mix_stride(int d) {
 // Least waves per SIMD to compile such kernels for.  The LDS rows of a
 // component pass through vector registers; left alone the compiler keeps so
 // many in flight that two or three waves fit, too few to issue side by
-// side.  Four waves (128 registers) hold 8-D and 12-D kernels without
-// spills and gain (8-D, 2^20 chains x 128 steps: 3.75 -> 3.4 ms, 12-D
-// 6.0 -> 5.7 ms); from d = 13 they spill (16-D 10 -> 20 ms), and three (168
-// registers) are best.
-__host__ __device__ constexpr int min_waves(bool split, int d) { return !split ? 1 : d <= 12 ? 4 : 3; }
+// side.  So as many waves as the kernel holds without spills, which goes by
+// the dimension and by the move (a gradient, the Hamiltonian momentum):
+// four (128 registers), three (168) or two (256).  8-D Langevin, 2^20
+// chains x 128 steps: 3.75 -> 3.4 ms with four; with spills there is nothing
+// to gain (16-D random walk at four waves 10 -> 20 ms; 16-D Hamiltonian at
+// three 20% slower than without the split).
+__host__ __device__ constexpr int min_waves(bool split, int loc, int d) {
+    if (!split) return 1;
+    if (loc == LOC_RWMH) return d <= 12 ? 4 : 3;
+    if (d <= 10) return 4;
+    return d <= (loc == LOC_MALA ? 13 : 12) ? 3 : 2;
+}
 // Dynamic LDS of the step and drain kernels: the target parameters when
 // they are staged (RESTORE_FLAG_PARAMS_LDS), rounded up to 4 floats, or the
 // LDS rows of K full-covariance components (split), then the learned mu's

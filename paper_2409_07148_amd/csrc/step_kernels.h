@@ -28,7 +28,7 @@ namespace restore {
 // Metropolis-Hastings reference chain M^l (no killing, large steps from mu
 // with probability l; see step_once).
 template <int D, int TGT, int LOC, int MU, bool LDS, bool MH = false, bool SPLIT = false>
-__global__ __launch_bounds__(256, (min_waves(SPLIT, D))) void step_kernel(StepArgs a, int n_param_floats) {
+__global__ __launch_bounds__(256, (min_waves(SPLIT, LOC, D))) void step_kernel(StepArgs a, int n_param_floats) {
     extern __shared__ __attribute__((aligned(16))) float smem[];
     const auto P = stage_target<D, LDS, SPLIT>(a, n_param_floats, smem);
     const auto MR = stage_mu<D, MU>(a, smem + mu_lds_offset(LDS, SPLIT, n_param_floats, D, a.n_comp));

@@ -50,6 +50,15 @@ def test_one_lane_drain_has_no_other_forms_registers(kernels):
             assert drain <= 1.15 * step + 8, (d, local, drain, step)
 
 
+def test_kernels_that_ask_for_waves_do_not_spill(kernels):
+    # the split kernels are compiled for a number of waves a SIMD
+    split = {k: v for k, v in kernels.items() if k[0] == "step_kernel" and k[1][6] == 1}
+    assert len(split) == 13 * 3 * 2 + 2 * 2   # d = 4..16, three moves, restore and MH; 8-D learned mu
+    batch = {k: v for k, v in kernels.items() if k[0].startswith("batch_") and k[1][-1] == 1}
+    assert len(batch) == 20
+    assert not {k: v for k, v in {**split, **batch}.items() if v["spill"]}
+
+
 def test_drain_over_lanes_does_not_spill(kernels):
     for d in range(1, 17):
         for local in (RWMH, MALA, HMC):

@@ -553,14 +553,29 @@ void fill_args(restore_ctx *c) {
     a.image_fx = c->splat.fixed ? at<unsigned long long>(c, c->lay.img_fx) : nullptr;
 }
 
-// Steps read a full-covariance slab half from LDS once there are waves to
-// issue side by side.  Below 2^16 chains a SIMD has at most one: the LDS
-// reads only add to its stream (Metropolis-Hastings steps of 7801 chains at
-// d = 2 and 23 799 at d = 3 run 9% and 11% slower with them; 76 916 chains
-// at d = 6 10% faster, 2^20 at d = 8 18%).  Drains keep to the scalar cache
-// too: all but their first steps run few waves.
-bool split_slab(const restore_ctx *c) {
-    return c->ks.step_split && !c->lds && c->cfg.n_chains >= (1LL << 16);
+// Fewest chains whose steps read a full-covariance slab half from LDS.  That
+// pays once waves issue side by side; a SIMD's only wave has the LDS reads in
+// its own stream.  Times without the split over times with it, K = 1 to 16,
+// per 32 steps:
+//   d <= 10, 65 536 chains (a wave a SIMD): 0.76 to 1.04
+//   d <= 10, 81 920: 0.98 to 1.10; 2^18: 1.00 to 1.25; 2^20: 1.04 to 1.24
+//   d = 9 and 10 random walk, d = 6 Hamiltonian: 0.90 to 1.05 up to two
+//     waves a SIMD, 1.01 to 1.10 at three
+//   d = 7 Hamiltonian: 0.87 to 1.04 at any size
+//   d >= 11: 0.96 to 1.28 from 65 536 on (16-D K = 2 to 16 1.05 to 1.25)
+//   learned mu (d = 8): Langevin 0.91 to 1.04 up to two waves a SIMD, 1.04
+//     to 1.20 from three; random walk 1.01 to 1.17 from 66 000
+//   Metropolis-Hastings: d <= 10 0.89 to 1.15 at 65 536, 1.00 to 1.28 from
+//     66 000; d >= 11 1.00 to 1.25 from 65 536
+// Drains keep to the scalar cache: all but their first steps run few waves.
+int64_t split_min_chains(const Validated &v, bool mh) {
+    constexpr int64_t one = SIMD_THREADS, two = 2 * SIMD_THREADS;   // waves a SIMD
+    if (v.d >= 11) return one;
+    if (mh) return one + 1;
+    if (v.mu == MU_GMM) return (v.loc == LOC_MALA ? two : one) + 1;
+    if (v.loc == LOC_HMC && v.d == 7) return INT64_MAX;
+    if ((v.loc == LOC_HMC && v.d == 6) || (v.loc == LOC_RWMH && v.d >= 9)) return two + 1;
+    return one + one / 4;
 }
 
 // Dynamic LDS bytes of a step or drain launch (mu_lds_offset in
@@ -797,15 +812,15 @@ static restore_status step_impl(restore_ctx *c, int32_t n_steps, int64_t n_recor
     a.rec_chains = n_record;
     int np = c->n_params;
     void *kargs[] = {&a, &np};
-    const bool split = split_slab(c);
-    const size_t shm = kernel_lds_bytes(c, c->lds, split);
+    // (the MH chain's parameters are not staged)
+    const bool split = (c->mh ? c->ks.step_mh_split != nullptr : c->ks.step_split && !c->lds) &&
+                       c->cfg.n_chains >= split_min_chains(c->v, c->mh);
+    const size_t shm = kernel_lds_bytes(c, c->lds && !c->mh, split);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (c->mh) {
         // the MH chain: parameters through the scalar cache, direct splats
-        const bool mh_split = c->ks.step_mh_split && c->cfg.n_chains >= (1LL << 16);
-        hipError_t e = hipLaunchKernel(mh_split ? c->ks.step_mh_split : c->ks.step_mh,
-                                       grid_for(c->cfg.n_chains, c->block), dim3(c->block), kargs,
-                                       kernel_lds_bytes(c, false, mh_split), s);
+        hipError_t e = hipLaunchKernel(split ? c->ks.step_mh_split : c->ks.step_mh,
+                                       grid_for(c->cfg.n_chains, c->block), dim3(c->block), kargs, shm, s);
         if (e != hipSuccess) return hip_fail(e, "MH step launch");
     } else if (c->splat.n_tiles) {
         // tile-stratified: an LDS copy of the workgroup's tile takes the splats

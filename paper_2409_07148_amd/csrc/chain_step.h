@@ -395,7 +395,9 @@ __device__ __forceinline__ void step_once(const StepArgs &a, PT P, uint32_t s,
     // the holding time dt = min(t1, t2) ~ Exp(1 + k) whichever clock fires;
     // with rb_dt its conditional mean 1 / (1 + k) is accumulated instead
     float dt = kill ? t2 : t1;
-    if (__builtin_expect(rb_dt != 0, 0)) dt = inv_k > 1e30f ? 1.0f : inv_k / (1.0f + inv_k);
+    // (out of the way in the short steps of small populations only: elsewhere
+    // the layout that follows had a lone wave's steps take up to 10% longer)
+    if (PRE ? __builtin_expect(rb_dt != 0, 0) : rb_dt) dt = inv_k > 1e30f ? 1.0f : inv_k / (1.0f + inv_k);
 
     bool large = false;
     if constexpr (MH) {

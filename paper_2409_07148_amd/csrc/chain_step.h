@@ -50,9 +50,19 @@ __device__ __forceinline__ auto stage_target(const StepArgs &a, int n_floats, fl
     if constexpr (SPLIT) {
         using R = MixRows<D>;
         const float *src = a.params + 1 + D + R::AT;
-        for (int i = threadIdx.x; i < a.n_comp * R::STRIDE; i += blockDim.x) {
-            const int k = i / R::STRIDE, e = i - k * R::STRIDE;
-            smem[i] = e < R::COUNT ? src[k * comp_stride(TGT_FULL, D) + e] : 0.0f;
+        const int n = a.n_comp * R::STRIDE;
+        // eight loads in flight per thread
+        for (int i0 = threadIdx.x; i0 < n; i0 += 8 * blockDim.x) {
+            float t[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int i = i0 + j * blockDim.x, k = i / R::STRIDE, e = i - k * R::STRIDE;
+                t[j] = 0.0f;
+                if (i < n && e < R::COUNT) t[j] = src[k * comp_stride(TGT_FULL, D) + e];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (i0 + j * blockDim.x < n) smem[i0 + j * blockDim.x] = t[j];
         }
         __syncthreads();
         return MixPtr{(const_fptr)a.params, (lds_fptr)smem};

@@ -160,9 +160,25 @@ __device__ __forceinline__ auto lane_target(const StepArgs &a, float *smem) {
     } else if constexpr (TGT == TGT_FULL) {
         static_assert(G == FULL_LANES, "four lanes a chain");
         constexpr int S = comp_stride(TGT_FULL, D);
-        const int n = a.n_comp * S, all = quad_slab_floats(D, a.n_comp);
-        for (int i = threadIdx.x; i < all; i += blockDim.x)
-            smem[i] = i < n ? a.params[i] : i % S == 0 ? -INFINITY : 0.0f;
+        // 16 bytes a thread, eight loads in flight (one float at a time, a
+        // wave's copy of a 12-D slab of 17 components took 10 us, as long as
+        // the drain of chains that are all killed at its first step)
+        typedef float v4f __attribute__((ext_vector_type(4)));
+        const int n4 = a.n_comp * S / 4, all4 = quad_slab_floats(D, a.n_comp) / 4;
+        const v4f *src = reinterpret_cast<const v4f *>(a.params);   // 256-byte aligned
+        v4f *dst = reinterpret_cast<v4f *>(smem);
+        for (int i0 = threadIdx.x; i0 < all4; i0 += 8 * blockDim.x) {
+            v4f t[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int i = i0 + k * blockDim.x;
+                t[k] = v4f{i % (S / 4) == 0 ? -INFINITY : 0.0f, 0.0f, 0.0f, 0.0f};
+                if (i < n4) t[k] = src[i];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (i0 + k * blockDim.x < all4) dst[i0 + k * blockDim.x] = t[k];
+        }
         __syncthreads();
         return QuadPtr{(lds_fptr)smem, (int)(threadIdx.x % G)};
     } else {

@@ -75,6 +75,8 @@ __host__ __device__ constexpr int mu_slab_floats(int d, int K) { return 4 + K * 
 // full-covariance mixtures; the unadjusted jump process.
 constexpr int FULL_LANES = 4;
 constexpr int INFLOW_LANES = 16;
+// Mixtures whose short drain lists take several lanes a chain.
+__host__ __device__ constexpr bool drains_wide(int tgt, int mu) { return tgt == TGT_FULL && mu == MU_UNIFORM; }
 // One wave on each SIMD of the chip (256 CUs of four), in threads.
 constexpr int64_t SIMD_THREADS = 1024LL * 64;
 // Waves a SIMD holds of them: from d = 13 a lane's component and state need

@@ -549,7 +549,8 @@ __global__ __launch_bounds__(256) void drain_kernel(StepArgs a, int n_param_floa
     if (blockIdx.x == 0 && threadIdx.x == 0) *count_zero = 0u;
     const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t n_in = a.list ? (int64_t)*a.list_count : a.n_chains;
-    if (n_in <= wide_max) {
+    // (only where there is such a kernel: the test costs the others registers)
+    if (drains_wide(TGT, MU) && !LDS && n_in <= wide_max) {
         if (at < n_in) list_out[at] = a.list[at];
         if (at == 0) {
             *count_out = (uint32_t)n_in;
@@ -667,7 +668,7 @@ static KernelSet make_set() {
     }
     k.drain = (const void *)drain_kernel<D, TGT, LOC, MU, false>;
     k.drain_lds = (const void *)drain_kernel<D, TGT, LOC, MU, true>;
-    if constexpr (TGT == TGT_FULL && MU == MU_UNIFORM) k.drain_wide = (const void *)drain_wide_kernel<D, TGT, LOC>;
+    if constexpr (drains_wide(TGT, MU)) k.drain_wide = (const void *)drain_wide_kernel<D, TGT, LOC>;
     if constexpr (TGT != TGT_PSS && MU == MU_UNIFORM) {
         k.rand_prepass = (const void *)rand_prepass_kernel<D>;
         k.step_pre = (const void *)step_pre_kernel<D, TGT, LOC, 1>;

@@ -267,19 +267,20 @@ __global__ __launch_bounds__(256, (lane_waves(TGT, D, G))) void drain_pre_kernel
     bool alive = (ch.status & ST_ALIVE) != 0u;
     unsigned long long n_t = 0, n_acc = 0, n_kill = 0;
     bool stepped = false, kill_last = false, acc_last = false;
-    // one drain step; false once no lane of the wave is alive
-    auto step = [&](int it, const StepRand<D> *r) {
+    // one drain step, its inputs from r or drawn; false once no lane of the
+    // wave is alive
+    auto step = [&](int it, const StepRand<D> *r, auto from_pre) __attribute__((always_inline)) {
         const unsigned long long live = __ballot(alive);
         if (live == 0ull) return false;
         n_t += __popcll(live);
         bool kill = false, accept = false;
         if (alive) {
-            if (r)
+            if constexpr (decltype(from_pre)::value)
                 step_once<D, TGT, LOC, MU_UNIFORM, true, PT, false, false, false, true>(
                     a, P, a.s0 + (uint32_t)it, (uint32_t)c, ch, kill, accept, r);
             else
                 step_once<D, TGT, LOC, MU_UNIFORM, true, PT>(a, P, a.s0 + (uint32_t)it, (uint32_t)c, ch,
-                                                                     kill, accept);
+                                                             kill, accept);
             stepped = true;
             kill_last = kill;
             acc_last = accept;
@@ -294,10 +295,10 @@ __global__ __launch_bounds__(256, (lane_waves(TGT, D, G))) void drain_pre_kernel
     int it = 0;
     if (n_pre > 0) {
         const PFT pf(pre, a.n_chains, chunk, c, n_pre - 1);
-        auto run = [&](const StepRand<D> (&r)[PF], int it0) {
+        auto run = [&](const StepRand<D> (&r)[PF], int it0) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < PF; ++j)
-                if (more && it0 + j < n_pre) more = step(it0 + j, &r[j]);
+                if (more && it0 + j < n_pre) more = step(it0 + j, &r[j], std::true_type{});
         };
         StepRand<D> A[PF], B[PF];
         pf.load(A, 0);
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(256, (lane_waves(TGT, D, G))) void drain_pre_kernel
         }
         it = n_pre;
     }
-    for (; more && it < a.n_steps; ++it) more = step(it, nullptr);
+    for (; more && it < a.n_steps; ++it) more = step(it, nullptr, std::false_type{});
     if (stepped) {
         ch.status = (ch.status & ~(ST_LAST_KILL | ST_LAST_ACCEPT | ST_ALIVE)) | (alive ? ST_ALIVE : 0u) |
                     (kill_last ? ST_LAST_KILL : 0u) | (acc_last ? ST_LAST_ACCEPT : 0u);

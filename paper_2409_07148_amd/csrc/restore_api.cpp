@@ -472,6 +472,7 @@ struct restore_ctx {
     char *base = nullptr;
     int n_params = 0;
     int block = 256;
+    int pre_block = 64;         // of the pre-pass kernels
     bool lds = false;
     int lanes = 1;              // lanes a chain of the pre-pass kernels
     bool drained = false;
@@ -551,6 +552,16 @@ void fill_args(restore_ctx *c) {
     a.bin_cap = (int32_t)c->splat.cap;
     a.n_bins = c->splat.n_bins;
     a.image_fx = c->splat.fixed ? at<unsigned long long>(c, c->lay.img_fx) : nullptr;
+}
+
+// Threads a workgroup of the pre-pass kernels by default: one wave while
+// there are SIMDs to spare, and 256, one wave for each SIMD of a CU, from half
+// a wave a SIMD on.  Single waves may be placed two to a SIMD although others
+// are free: drains of 50 000 and 65 000 chains took 446 us in one build and
+// 555 in another of the same steps, by the kernel's registers alone, and 437
+// to 467 in workgroups of 256 in both.
+int pre_block_for(const restore_config *cfg, int64_t threads) {
+    return cfg->block_size ? cfg->block_size : threads <= SIMD_THREADS / 2 ? 64 : 256;
 }
 
 // Fewest chains whose steps read a full-covariance slab half from LDS.  That
@@ -743,6 +754,7 @@ restore_status restore_init(restore_ctx **out, const restore_target *target, con
     // several lanes a chain while every SIMD can hold its waves at once
     if (ks.step_lanes && cfg->n_chains * ks.lanes <= SIMD_THREADS * lane_waves(v.tgt, v.d, ks.lanes))
         c->lanes = ks.lanes;
+    c->pre_block = pre_block_for(cfg, cfg->n_chains * c->lanes);
     fill_args(c);
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -833,8 +845,8 @@ static restore_status step_impl(restore_ctx *c, int32_t n_steps, int64_t n_recor
         // from one half of the pre-pass buffer while extra workgroups of the
         // same launch fill the other half with the next chunk
         int chunk = c->rand.chunk;
-        const int64_t step_blocks = (c->cfg.n_chains * c->lanes + c->block - 1) / c->block;
-        const int64_t gen_blocks = (c->cfg.n_chains + c->block - 1) / c->block *
+        const int64_t step_blocks = (c->cfg.n_chains * c->lanes + c->pre_block - 1) / c->pre_block;
+        const int64_t gen_blocks = (c->cfg.n_chains + c->pre_block - 1) / c->pre_block *
                                    ((chunk + PRE_GEN_STEPS - 1) / PRE_GEN_STEPS);
         for (int32_t done = 0; done < n_steps; done += chunk) {
             const int64_t s_first = c->steps_taken + done;
@@ -846,7 +858,7 @@ static restore_status step_impl(restore_ctx *c, int32_t n_steps, int64_t n_recor
             PreGen g{rand_half(c, 1 - c->pre_half), (uint32_t)(s_first + a.n_steps), chunk, (int32_t)step_blocks};
             void *sargs[] = {&a, &cur, &chunk, &g};
             hipError_t e = hipLaunchKernel(c->lanes > 1 ? c->ks.step_lanes : c->ks.step_pre,
-                                           dim3((unsigned)(step_blocks + gen_blocks)), dim3(c->block), sargs,
+                                           dim3((unsigned)(step_blocks + gen_blocks)), dim3(c->pre_block), sargs,
                                            lanes_lds_bytes(c), s);
             if (e != hipSuccess) return hip_fail(e, "step launch");
             c->pre_half = 1 - c->pre_half;
@@ -927,7 +939,7 @@ restore_status restore_drain(restore_ctx *c, void *stream) {
         int chunk = c->rand.chunk, np = n_pre;
         void *kargs[] = {&a, &cur, &chunk, &np};
         hipError_t e = hipLaunchKernel(c->lanes > 1 ? c->ks.drain_lanes : c->ks.drain_pre,
-                                       grid_for(c->cfg.n_chains * c->lanes, c->block), dim3(c->block), kargs,
+                                       grid_for(c->cfg.n_chains * c->lanes, c->pre_block), dim3(c->pre_block), kargs,
                                        lanes_lds_bytes(c), s);
         if (e != hipSuccess) return hip_fail(e, "drain launch");
         c->drained = true;

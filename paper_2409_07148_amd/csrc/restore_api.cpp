@@ -564,6 +564,30 @@ int pre_block_for(const restore_config *cfg, int64_t threads) {
     return cfg->block_size ? cfg->block_size : threads <= SIMD_THREADS / 2 ? 64 : 256;
 }
 
+// Whether a small population takes several lanes a chain: while every SIMD
+// holds their waves at once and, for full covariances, where a pass of four
+// components is full enough for the waves there are.  Times of 64 steps with
+// one lane over times with four, d = 1 to 16, the three moves:
+//   K = 1: 0.85 to 1.18 up to 8192 chains, 0.63 to 1.1 at 16 384
+//   K = 2: 1.00 to 1.5 up to 8192 chains, 0.92 to 1.25 at 12 000
+//   K >= 3: 0.97 to 2.7 up to 12 000
+//   K >= 3, 16 384 chains: 1.02 to 2.3 but for the random walk up to d = 3
+//     (0.88 to 1.14) and, for K < 7, where a SIMD holds one such wave and
+//     the next chunk's inputs have to wait (0.85 to 1.09)
+//   20 000 to 32 768 chains: K >= 7 0.96 to 1.8 but for that random walk
+//     (0.91 to 1.08) and Langevin moves from d = 6 on (K = 7 0.93 to 1.4,
+//     K = 16 1.2 to 1.5); K = 3 to 5 0.82 to 1.45
+bool over_lanes(const Validated &v, int64_t n, int lanes) {
+    const int waves = lane_waves(v.tgt, v.loc, v.d, lanes);
+    if (n * lanes > SIMD_THREADS * waves) return false;
+    if (v.tgt != TGT_FULL) return true;
+    if (n <= 8192) return v.K >= 2;
+    if (n <= 12288) return v.K >= 3;
+    if (v.loc == LOC_RWMH && v.d <= 3) return false;
+    if (n <= 16384 && waves == 2) return v.K >= 3;
+    return v.K >= (v.loc == LOC_MALA && v.d >= 6 && n > 16384 ? 16 : 7);
+}
+
 // Fewest chains whose steps read a full-covariance slab half from LDS.  That
 // pays once waves issue side by side; a SIMD's only wave has the LDS reads in
 // its own stream.  Times without the split over times with it, K = 1 to 16,
@@ -751,9 +775,7 @@ restore_status restore_init(restore_ctx **out, const restore_target *target, con
     c->mu = *mu;
     c->splat = sp;
     c->rand = ks.step_pre ? rp : RandPlan{};
-    // several lanes a chain while every SIMD can hold its waves at once
-    if (ks.step_lanes && cfg->n_chains * ks.lanes <= SIMD_THREADS * lane_waves(v.tgt, v.d, ks.lanes))
-        c->lanes = ks.lanes;
+    if (ks.step_lanes && over_lanes(v, cfg->n_chains, ks.lanes)) c->lanes = ks.lanes;
     c->pre_block = pre_block_for(cfg, cfg->n_chains * c->lanes);
     fill_args(c);
 

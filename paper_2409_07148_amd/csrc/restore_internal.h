@@ -79,10 +79,14 @@ constexpr int INFLOW_LANES = 16;
 __host__ __device__ constexpr bool drains_wide(int tgt, int mu) { return tgt == TGT_FULL && mu == MU_UNIFORM; }
 // One wave on each SIMD of the chip (256 CUs of four), in threads.
 constexpr int64_t SIMD_THREADS = 1024LL * 64;
-// Waves a SIMD holds of them: from d = 13 a lane's component and state need
-// the registers of two.
-__host__ __device__ constexpr int lane_waves(int tgt, int d, int lanes) {
-    return lanes > 1 && !(tgt == TGT_FULL && d > 12) ? 2 : 1;
+// Waves a SIMD holds of them without spills: a lane's component and state
+// need the registers of two from d = 13 on, with a gradient from 12, with a
+// Hamiltonian momentum from 11 (and at 8, where the next component is read
+// ahead).
+__host__ __device__ constexpr int lane_waves(int tgt, int loc, int d, int lanes) {
+    if (lanes == 1) return 1;
+    const bool one = d >= 13 || (loc == LOC_MALA && d == 12) || (loc == LOC_HMC && (d >= 11 || d == 8));
+    return tgt == TGT_FULL && one ? 1 : 2;
 }
 // Floats of a full-covariance slab in LDS with four lanes a chain: whole
 // passes of four components.

@@ -193,7 +193,7 @@ __device__ __forceinline__ auto lane_target(const StepArgs &a, float *smem) {
 // one is loaded while the other's steps run.  The same chains as
 // step_kernel, bit for bit.
 template <int D, int TGT, int LOC, int G>
-__global__ __launch_bounds__(256, (lane_waves(TGT, D, G))) void step_pre_kernel(StepArgs a, const float *pre, int chunk, PreGen g) {
+__global__ __launch_bounds__(256, (lane_waves(TGT, LOC, D, G))) void step_pre_kernel(StepArgs a, const float *pre, int chunk, PreGen g) {
     if ((int64_t)blockIdx.x >= g.step_blocks) {
         pregen_block<D>(a, g, chunk);
         return;
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256, (lane_waves(TGT, D, G))) void step_pre_kernel(
 // them inline.  A wave ends when its last lane's tour is killed; survivors
 // of all a.n_steps steps are censored.  The same chains as drain_kernel.
 template <int D, int TGT, int LOC, int G>
-__global__ __launch_bounds__(256, (lane_waves(TGT, D, G))) void drain_pre_kernel(StepArgs a, const float *pre, int chunk, int n_pre) {
+__global__ __launch_bounds__(256, (lane_waves(TGT, LOC, D, G))) void drain_pre_kernel(StepArgs a, const float *pre, int chunk, int n_pre) {
     using PFT = PreFetch<D>;
     constexpr int PF = PFT::PF;
     extern __shared__ __attribute__((aligned(16))) float smem[];

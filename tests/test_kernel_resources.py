@@ -59,7 +59,8 @@ def test_kernels_that_ask_for_waves_do_not_spill(kernels):
     assert not {k: v for k, v in {**split, **batch}.items() if v["spill"]}
 
 
-def test_drain_over_lanes_does_not_spill(kernels):
+def test_kernels_over_lanes_do_not_spill(kernels):
     for d in range(1, 17):
         for local in (RWMH, MALA, HMC):
-            assert kernels["drain_wide_kernel", (d, FULL, local)]["spill"] == 0, (d, local)
+            for kernel, args in (("drain_wide_kernel", ()), ("step_pre_kernel", (4,)), ("drain_pre_kernel", (4,))):
+                assert kernels[kernel, (d, FULL, local) + args]["spill"] == 0, (kernel, d, local)

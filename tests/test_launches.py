@@ -57,3 +57,30 @@ def test_which_populations_read_the_slab_half_from_lds(tmp_path):
         name, lds = _step_kernel(rec)
         assert _is_split(name) == split, (run, name)
         assert (lds > 0) == (split or run["problem"].get("flags") == 1), (run, lds)
+
+
+def test_which_small_populations_take_four_lanes(tmp_path):
+    # (d, move, K) and the most chains that do
+    limits = [(2, "rwmh", 1, 0), (2, "rwmh", 2, 8192), (3, "rwmh", 16, 12288), (4, "rwmh", 3, 16384),
+              (2, "mala", 5, 16384), (2, "mala", 7, 32768), (5, "hmc", 2, 8192), (5, "hmc", 3, 16384),
+              (5, "hmc", 7, 32768), (8, "hmc", 5, 12288), (8, "hmc", 7, 16384), (12, "rwmh", 3, 16384),
+              (12, "mala", 5, 12288), (13, "rwmh", 7, 16384),
+              (6, "mala", 7, 16384), (6, "mala", 16, 32768)]
+    runs, want = [], []
+    for d, local, K, limit in limits:
+        for n in (limit, limit + 1) if limit else (500,):
+            run = _full(d, local, n)
+            run["args"]["K"] = K
+            run["with"]["drain_cap"] = 40
+            runs.append({**run, "drain": True})
+            want.append(n <= limit)
+    for run, rec, lanes in zip(runs, record(tmp_path, runs), want):
+        for launch, kernel in ((rec["step_launches"][-1], "step_pre_kernel"), (rec["drain_launches"][-1], "drain_pre_kernel")):
+            name, grid, block, lds = launch
+            n, d = run["args"]["n_chains"], run["args"]["d"]
+            assert kernel in name and (lds > 0) == lanes and f"ELi{4 if lanes else 1}EEEv" in name, (run, launch)
+            # a workgroup of 256 once the lanes fill half the SIMDs
+            threads = n * (4 if lanes else 1)
+            assert block == (256 if threads > 32768 else 64), (run, launch)
+            if kernel == "drain_pre_kernel":
+                assert grid == -(-threads // block)

@@ -79,11 +79,14 @@ __device__ __forceinline__ void draw_step(uint32_t step, uint32_t chain, uint32_
 }
 
 // The correctly rounded square root of x >= 2^-96 (and +0), the value of
-// sqrtf: the hardware root s is within one ulp, and s - ulp / 2 and
-// s + ulp / 2 lie on the far side of the root when x - s pred(s) <= 0 and
-// x - s succ(s) > 0 (one rounding each).  Nine instructions, against the
-// library's sixteen, which also cover smaller numbers and infinities; every
-// float of [2^-96, 64] gives the same bits.
+// sqrtf, by Tuckerman's test (Agarwal et al., New scalar and vector elementary
+// functions for the IBM System/370, IBM J. Res. Develop. 30, 1986): s is the
+// rounded root when s pred(s) < x <= s succ(s), and the hardware root is
+// within one ulp of it, so one of s and its neighbours passes.  Each product
+// is subtracted from x with one rounding, which keeps the sign.  Nine
+// instructions, against the library's sixteen, which also cover smaller
+// numbers and infinities; every float of [2^-96, 64] gives the same bits as
+// sqrtf and as the float64 root (tests/test_gpu_sqrt.py).
 __device__ __forceinline__ float sqrt_normal(float x) {
     const float s = __builtin_amdgcn_sqrtf(x);
     const float dn = __uint_as_float(__float_as_uint(s) - 1u), up = __uint_as_float(__float_as_uint(s) + 1u);
